@@ -64,6 +64,10 @@ CBIC_HD __forceinline__ float dsqrt(float v) { return sqrtf(v); }
 CBIC_HD __forceinline__ bool dfinite(double v) { return isfinite(v); }
 CBIC_HD __forceinline__ bool dfinite(float v) { return isfinite(v); }
 
+// 64-bit DPP move (the compiler's builtin takes 32-bit values only): old value,
+// source, control, row mask, bank mask, bound control
+__device__ long dpp_update_i64(long old, long v, int ctrl, int rm, int bm, bool bc) __asm("llvm.amdgcn.update.dpp.i64");
+
 template <class R>
 CBIC_HD __forceinline__ R dmax(R a, R b) { return a > b ? a : b; }
 

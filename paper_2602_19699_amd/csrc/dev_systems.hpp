@@ -293,7 +293,11 @@ struct Arm3 {
       }
     }
 
+    // constants of the Riccati step: dt, the clipped control Hessian (2 w_u)
+    // and the clipped velocity Hessian (zero)
     CBIC_HD __forceinline__ R step_dt() const { return R(p[0]); }
+    CBIC_HD __forceinline__ R ctrl_hess(R eps) const { return dmax(R(2) * R(p[10]), eps); }
+    CBIC_HD __forceinline__ R vel_hess(R eps) const { return dmax(R(0), eps); }
 
     // Jacobians of the velocity update qd+ = qd + dt qdd: V = d qd+ / d(q, qd)
     // (3 x 6), W = d qd+ / d tau (3 x 3).  With q+ = q + dt qd+ the full

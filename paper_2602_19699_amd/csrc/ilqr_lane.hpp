@@ -519,6 +519,295 @@ struct Lane {
     return bad;
   }
 
+  // ------------------------------------------------------------------ backward, one lane per column
+  // riccati_step_si for the 6-state, 3-control system with the step's columns
+  // spread over the 16 lanes of a DPP row (a group of GL = 16): lanes 0..5
+  // hold the state columns, lanes 6..8 the control columns, lanes 9..15 the
+  // feedforward column (the same values in each).  A lane keeps its column of
+  // P and its entry of p; the columns of [P A | P B], C^T [P A | P B] and of
+  // [Q_xx; Q_ux | Q_xu; Q_uu] come from one code path for both kinds of
+  // column, and each lane solves for its own column of [K | k].  Values of
+  // another column are taken by row broadcasts (row_newbcast), which v_fmac
+  // reads as an operand; every entry comes from the same formula, in the same
+  // order, as in riccati_step_si, so the results agree bit for bit.
+  //
+  // Bound: the recursion is a serial chain of T steps and the batch gives one
+  // wave per SIMD, so a step costs what one wave takes to issue it.  The split
+  // over a lane pair issues about 690 instructions per step in FP32, this one
+  // 240 (FP64 275): 4096 arm instances of horizons 50..200, mixed, 20.3 ->
+  // 13.7 ms per solve; 500 in FP64 with 50 iterations 33.4 -> 25.7 ms.  Narrower
+  // groups do not hold nine columns and keep the lane pair.
+  template <int GL>
+  static constexpr bool kRow = GL == 16 && Sys::kSemiImplicit && N == 6 && M == 3;
+  // stride of a staged derivative block: whole 16-byte pieces for the row
+  // split's wide loads (44: sixteen blocks start on sixteen different banks)
+  template <int GL>
+  static constexpr int kBlk = kRow<GL> ? 44 : Model::ND;
+
+  // the value held by lane L of the 16-lane row
+  template <int L>
+  __device__ static __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x150 + L, 0xF, 0xF, true));
+  }
+  template <int L>
+  __device__ static __forceinline__ double row_bcast(double v) {
+    return __builtin_bit_cast(double, dpp_update_i64(0L, __builtin_bit_cast(long, v), 0x150 + L, 0xF, 0xF, true));
+  }
+  // lane i takes the value of lane i + 3 of its row (row_shl:3)
+  __device__ static __forceinline__ float row_shl3(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x103, 0xF, 0xF, true));
+  }
+  __device__ static __forceinline__ double row_shl3(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp(int(b), 0x103, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(int(b >> 32), 0x103, 0xF, 0xF, true);
+    return __longlong_as_double(static_cast<long long>(static_cast<unsigned>(lo)) |
+                                (static_cast<long long>(hi) << 32));
+  }
+
+  // acc[i] = fma(s_c of lane i, m_c, acc[i]) for c = 0, 1, 2 in turn and
+  // i = 0..5 (the s_nop covers the two wait states between a vector write of
+  // s_c and its DPP read)
+#define CBIC_ROW6(OP, S, Q)                                                     \
+  OP " %0, " S ", " Q " row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"          \
+  OP " %1, " S ", " Q " row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"          \
+  OP " %2, " S ", " Q " row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"          \
+  OP " %3, " S ", " Q " row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"          \
+  OP " %4, " S ", " Q " row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"          \
+  OP " %5, " S ", " Q " row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+  __device__ static __forceinline__ void row_fma18(R (&a)[N], R s0, R s1, R s2, R m0, R m1, R m2) {
+    if constexpr (sizeof(R) == 4)
+      asm("s_nop 1\n\t" CBIC_ROW6("v_fmac_f32_dpp", "%6", "%9") CBIC_ROW6("v_fmac_f32_dpp", "%7", "%10")
+              CBIC_ROW6("v_fmac_f32_dpp", "%8", "%11")
+          : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5])
+          : "v"(s0), "v"(s1), "v"(s2), "v"(m0), "v"(m1), "v"(m2));
+    else
+      asm("s_nop 1\n\t" CBIC_ROW6("v_fmac_f64_dpp", "%6", "%9") CBIC_ROW6("v_fmac_f64_dpp", "%7", "%10")
+              CBIC_ROW6("v_fmac_f64_dpp", "%8", "%11")
+          : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5])
+          : "v"(s0), "v"(s1), "v"(s2), "v"(m0), "v"(m1), "v"(m2));
+  }
+#undef CBIC_ROW6
+  // a = fma(s of lane c, m_c, a) for c = 0, 1, 2 in turn
+  __device__ static __forceinline__ void row_fma3(R& a, R s, R m0, R m1, R m2) {
+#define CBIC_ROW1(OP, C, Q) OP " %0, %1, " Q " row_newbcast:" C " row_mask:0xf bank_mask:0xf\n\t"
+    if constexpr (sizeof(R) == 4)
+      asm("s_nop 1\n\t" CBIC_ROW1("v_fmac_f32_dpp", "0", "%2") CBIC_ROW1("v_fmac_f32_dpp", "1", "%3")
+              CBIC_ROW1("v_fmac_f32_dpp", "2", "%4")
+          : "+v"(a)
+          : "v"(s), "v"(m0), "v"(m1), "v"(m2));
+    else
+      asm("s_nop 1\n\t" CBIC_ROW1("v_fmac_f64_dpp", "0", "%2") CBIC_ROW1("v_fmac_f64_dpp", "1", "%3")
+              CBIC_ROW1("v_fmac_f64_dpp", "2", "%4")
+          : "+v"(a)
+          : "v"(s), "v"(m0), "v"(m1), "v"(m2));
+#undef CBIC_ROW1
+  }
+
+  // what a lane of the row split keeps over the sweep
+  struct RowLane {
+    R P[N], p;               // its column of P, its entry of p (state columns)
+    R q3[3], qu[M];          // constant parts of its column of [Q_xx; Q_ux | .; Q_uu]: rows 3..5 and the control rows
+    int ov, sv, ol, oq[3];   // offsets into a derivative block: its column of [V | W] and stride, gradient, Q_xx rows 0..2
+    R* g;                    // its column of [K_k | k_k] at the current step
+    int gs, gk;              // strides of g between rows and between steps
+  };
+
+  __device__ static __forceinline__ void row_init(RowLane& L, const LaneState<R>& w, int s, int T, int r, R ev, R ru,
+                                                  const R (&P)[N][N], const R (&p)[N]) {
+    const bool state = r < N, ctrl = r >= N && r < N + M;
+    const int j = state ? r : 0, m = ctrl ? r - N : (state ? 0 : M - 1);
+    L.p = p[0];
+#pragma unroll
+    for (int i = 0; i < N; ++i) L.P[i] = P[i][0];
+#pragma unroll
+    for (int c = 1; c < N; ++c)
+      if (r == c) {
+        L.p = p[c];
+#pragma unroll
+        for (int i = 0; i < N; ++i) L.P[i] = P[i][c];
+      }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      L.q3[i] = r == 3 + i ? ev : R(0);
+      L.qu[i] = ctrl && m == i ? ru : R(0);
+      // row i of the position Hessian's upper triangle (columns 0..2); the
+      // other columns' rows are zero (the block's zero entry)
+      const int a = i < j ? i : j, b = i < j ? j : i;
+      L.oq[i] = r < 3 ? 30 + (a == 0 ? b : (a == 1 ? 2 + b : 5)) : 39;
+    }
+    L.ov = state ? j : 18 + m;
+    L.sv = state ? N : M;
+    L.ol = r < 3 ? 27 + r : (ctrl ? 36 + m : 39);
+    L.g = state ? Kp(w, T - 1, s) + j : kp(w, T - 1, s);
+    L.gs = state ? N : 1;
+    L.gk = state ? M * N : M;
+  }
+
+  template <bool BOX>
+  __device__ static __forceinline__ uint32_t riccati_step_si_row(RowLane& L, R dt, const R* D, double mu,
+                                                                 const R (&u)[M], double umax, int r) {
+    static_assert(N == 6 && M == 3, "the column split is laid out for 6 states and 3 controls");
+    const bool pos = r < 3, state = r < N;
+    // the block's [V | W] column by column of this lane, and whole for the rows
+    const R v0 = D[L.ov], v1 = D[L.ov + L.sv], v2 = D[L.ov + 2 * L.sv];
+    const R lx = D[L.ol];
+    R q[N + M];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) q[i] = D[L.oq[i]];
+    R VW[3][N + M];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) VW[c][i] = D[c * N + i];
+#pragma unroll
+      for (int m = 0; m < M; ++m) VW[c][N + m] = D[18 + c * M + m];
+    }
+    // row r of P C (P is symmetric: its row is the lane's column), C^T p
+    const R pc0 = dt * L.P[0] + L.P[3], pc1 = dt * L.P[1] + L.P[4], pc2 = dt * L.P[2] + L.P[5];
+    const R pv = row_shl3(L.p);
+    const R cp = dt * L.p + pv;
+    // column of [P A | P B]
+    R pa[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) pa[i] = pos ? L.P[i] : R(0);
+    row_fma18(pa, pc0, pc1, pc2, v0, v1, v2);
+    const R c0 = dt * pa[0] + pa[3], c1 = dt * pa[1] + pa[4], c2 = dt * pa[2] + pa[5];
+    // entry of [Q_x; Q_u] (x + (-0) leaves every x as it is)
+    R qx = lx + (pos ? L.p : R(-0.0));
+    row_fma3(qx, cp, v0, v1, v2);
+    // column of [Q_xx; Q_ux | .; Q_uu]
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      q[i] = q[i] + pa[i];
+      q[3 + i] = L.q3[i];
+      q[N + i] = L.qu[i];
+    }
+    const R cc[3] = {c0, c1, c2};
+#pragma unroll
+    for (int i = 0; i < N + M; ++i)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[i] += VW[c][i] * cc[c];
+    // Q_uu (upper triangle) and its factor in every lane
+    double Quu[M][M];
+    Quu[0][0] = double(row_bcast<6>(q[N]));
+    Quu[0][1] = double(row_bcast<7>(q[N]));
+    Quu[0][2] = double(row_bcast<8>(q[N]));
+    Quu[1][1] = double(row_bcast<7>(q[N + 1]));
+    Quu[1][2] = double(row_bcast<8>(q[N + 1]));
+    Quu[2][2] = double(row_bcast<8>(q[N + 2]));
+    if (mu != 0.0)
+#pragma unroll
+      for (int i = 0; i < M; ++i) Quu[i][i] += mu;
+    constexpr int NR = sizeof(R) == 4 ? 1 : 2;
+    double Lc[M][M], invd[M];
+    uint32_t bad = chol_fp64<M, NR>(Quu, Lc, invd) ? 0u : ST_CHOL_FAIL;
+    // right-hand sides: Q_ux's column in the state lanes, Q_u in lanes 9..15
+    const R Qu[M] = {row_bcast<6>(qx), row_bcast<7>(qx), row_bcast<8>(qx)};
+    R rhs[M], kc[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) rhs[i] = state ? q[N + i] : Qu[i];
+    bool solved = false;
+    if constexpr (sizeof(R) == 4) {
+      float lf[M][M], ivf[M];
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        ivf[i] = float(invd[i]);
+#pragma unroll
+        for (int j = 0; j < M; ++j) lf[i][j] = float(Lc[i][j]);
+      }
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        float v = rhs[i];
+#pragma unroll
+        for (int k2 = 0; k2 < i; ++k2) v -= lf[i][k2] * kc[k2];
+        kc[i] = v * ivf[i];
+      }
+#pragma unroll
+      for (int i = M - 1; i >= 0; --i) {
+        float v = kc[i];
+#pragma unroll
+        for (int k2 = i + 1; k2 < M; ++k2) v += lf[k2][i] * kc[k2];
+        kc[i] = v * -ivf[i];
+      }
+      solved = true;
+      if constexpr (BOX) {
+        const R kk[M] = {row_bcast<9>(kc[0]), row_bcast<9>(kc[1]), row_bcast<9>(kc[2])};
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+          const double d = double(kk[i]);
+          solved = solved && d >= -umax - double(u[i]) && d <= umax - double(u[i]);
+        }
+      }
+    }
+    if (!solved) {
+      unsigned held = 0;
+      double kb[M];
+      if constexpr (BOX) {
+        double g[M], lo[M], hi[M];
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+          kb[i] = double(Qu[i]);
+          g[i] = double(Qu[i]);
+          lo[i] = -umax - double(u[i]);
+          hi[i] = umax - double(u[i]);
+        }
+        chol_solve_neg_fp64<M>(Lc, invd, kb);
+        if (!box_qp<M, NR>(Quu, g, lo, hi, kb, held, Lc, invd) && !bad) bad = ST_CHOL_FAIL;
+      }
+      double col[M];
+#pragma unroll
+      for (int i = 0; i < M; ++i) col[i] = ((held >> i) & 1u) ? 0.0 : double(rhs[i]);
+      chol_solve_neg_fp64<M>(Lc, invd, col);
+#pragma unroll
+      for (int i = 0; i < M; ++i) kc[i] = R(BOX && !state ? kb[i] : col[i]);
+    }
+    const bool fin = dfinite(kc[0]) & dfinite(kc[1]) & dfinite(kc[2]);
+    // the control lanes carry the feedforward column as well (unused there)
+    if (!fin && !bad) bad = ST_NONFINITE;
+    L.g[0] = kc[0];
+    L.g[L.gs] = kc[1];
+    L.g[2 * L.gs] = kc[2];
+    L.g -= L.gk;
+    // p = Q_x + Q_ux^T k, P = sym(Q_xx + Q_ux^T K): rows i <= j of the column
+    // (the control lanes' columns are not used)
+    R pn = qx;
+    {
+      const R k0 = row_bcast<9>(kc[0]), k1 = row_bcast<9>(kc[1]), k2 = row_bcast<9>(kc[2]);
+      pn += q[N] * k0;
+      pn += q[N + 1] * k1;
+      pn += q[N + 2] * k2;
+    }
+    L.p = pn;
+    R po[N] = {q[0], q[1], q[2], q[3], q[4], q[5]};
+    row_fma18(po, q[N], q[N + 1], q[N + 2], kc[0], kc[1], kc[2]);
+    // rows i > j from the lanes that hold them as columns
+#pragma unroll
+    for (int i = 0; i < N; ++i) L.P[i] = po[i];
+    const bool e0 = r == 0, e1 = r == 1, e2 = r == 2, e3 = r == 3, e4 = r == 4;
+    row_patch<1>(L.P[1], po[0], e0);
+    row_patch<2>(L.P[2], po[0], e0);
+    row_patch<3>(L.P[3], po[0], e0);
+    row_patch<4>(L.P[4], po[0], e0);
+    row_patch<5>(L.P[5], po[0], e0);
+    row_patch<2>(L.P[2], po[1], e1);
+    row_patch<3>(L.P[3], po[1], e1);
+    row_patch<4>(L.P[4], po[1], e1);
+    row_patch<5>(L.P[5], po[1], e1);
+    row_patch<3>(L.P[3], po[2], e2);
+    row_patch<4>(L.P[4], po[2], e2);
+    row_patch<5>(L.P[5], po[2], e2);
+    row_patch<4>(L.P[4], po[3], e3);
+    row_patch<5>(L.P[5], po[3], e3);
+    row_patch<5>(L.P[5], po[4], e4);
+    return bad;
+  }
+  template <int C>
+  __device__ static __forceinline__ void row_patch(R& dst, R src, bool mine) {
+    const R v = row_bcast<C>(src);
+    dst = mine ? v : dst;
+  }
+
   // The control step and the (P, p) update from the step's Q blocks (Q_xx
   // and Q_uu upper triangles): Cholesky of Q_uu (+ mu I in the
   // Levenberg-Marquardt variant) in FP64 (one Newton step on the reciprocal
@@ -990,13 +1279,20 @@ struct Lane {
           ld(pu[q], up(w, buf, k, s));
         }
       }
-      uint32_t chunk_bad = 0;  // first failure in the chunk (axis-pair steps)
+      uint32_t chunk_bad = 0;  // first failure in the chunk
+      constexpr int BLK = kBlk<GL>;
+      // a lane of the row split sees its own column's failures only: the first
+      // one and its step
+      uint32_t row_bad = ~0u;
+      RowLane rl;
+      if constexpr (kRow<GL>) row_init(rl, w, s, T, r, mdl.vel_hess(eps), mdl.ctrl_hess(eps), P, p);
       for (int kc = T - 1; kc >= 0; kc -= C) {
 #pragma unroll
         for (int q = 0; q < PB; ++q)
           if (kc - (r + q * GL) >= 0) {
-            mdl.pack_derivs(px[q], pu[q], stage + (r + q * GL) * ND, eps);
-            if constexpr (BOX) st(stage + C * ND + (r + q * GL) * M, pu[q]);
+            mdl.pack_derivs(px[q], pu[q], stage + (r + q * GL) * BLK, eps);
+            if constexpr (kRow<GL>) stage[(r + q * GL) * BLK + ND] = R(0);  // the zero entry
+            if constexpr (BOX) st(stage + C * BLK + (r + q * GL) * M, pu[q]);
           }
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
@@ -1010,14 +1306,17 @@ struct Lane {
         const int cn = kc + 1 < C ? kc + 1 : C;
         for (int q = 0; q < cn; ++q) {
           R uq[M] = {};
-          if constexpr (BOX) ld(uq, stage + C * ND + q * M);
+          if constexpr (BOX) ld(uq, stage + C * BLK + q * M);
           if constexpr (Sys::kAxisPairs) {
             const uint32_t b =
-                axis_step<GL, BOX>(w, s, kc - q, stage + q * ND, uq, AP, h, dt, dt2, ev, ru, true, mu, umax);
+                axis_step<GL, BOX>(w, s, kc - q, stage + q * BLK, uq, AP, h, dt, dt2, ev, ru, true, mu, umax);
             if (!chunk_bad) chunk_bad = b;
+          } else if constexpr (kRow<GL>) {
+            const uint32_t b = riccati_step_si_row<BOX>(rl, dt, stage + q * BLK, mu, uq, umax, r);
+            if (b && row_bad == ~0u) row_bad = (uint32_t(q) << 8) | b;
           } else if constexpr (Sys::kSemiImplicit) {
             R V[N / 2][N], W[N / 2][M], lx[N], lu[M], Qc[N][N], Rc[M][M];
-            mdl.unpack_derivs_si(stage + q * ND, V, W, lx, lu, Qc, Rc, eps);
+            mdl.unpack_derivs_si(stage + q * BLK, V, W, lx, lu, Qc, Rc, eps);
             // every lane stores the gains (the group's lanes hold the same
             // values): no branch per step; a failure ends the sweep at the
             // end of the chunk
@@ -1029,12 +1328,21 @@ struct Lane {
             if (!chunk_bad) chunk_bad = b;
           } else {
             R A[N][N], B[N][M], lx[N], lu[M], Qc[N][N], Rc[M][M];
-            mdl.unpack_derivs(stage + q * ND, A, B, lx, lu, Qc, Rc, eps);
+            mdl.unpack_derivs(stage + q * BLK, A, B, lx, lu, Qc, Rc, eps);
             const uint32_t bad = riccati_step<BOX>(w, s, kc - q, A, B, lx, lu, Qc, Rc, P, p, store, mu, uq, umax);
             if (bad) return bad;
           }
         }
         stage_sync();
+        if constexpr (kRow<GL>) {
+          // the group's first failing step; a failed factor shows in every
+          // lane, so the lanes that stop at that step agree on the reason
+          if (__ballot(row_bad != ~0u)) {
+#pragma unroll
+            for (int o = 1; o < GL; o <<= 1) row_bad = min(row_bad, uint32_t(__shfl_xor(int(row_bad), o, 64)));
+            if (row_bad != ~0u) chunk_bad = row_bad & 0xFFu;
+          }
+        }
         if (chunk_bad) return chunk_bad;
       }
       return 0;
@@ -1370,7 +1678,7 @@ __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ pr
   // and the line search's step-record ring; the area stride is padded so that
   // the groups of a wave start on different banks
   constexpr int CT = GL * LN::PT;
-  constexpr int DS = staged ? C * (ND + (BOX ? LN::M : 0)) : 0;
+  constexpr int DS = staged ? C * (LN::template kBlk<GL> + (BOX ? LN::M : 0)) : 0;
   constexpr int AREA = DS > 2 * CT * LN::SWP ? DS : 2 * CT * LN::SWP;
   constexpr int STRIDE = (AREA + 31) / 32 * 32 + 4;
   __shared__ __align__(16) R stage_mem[(64 / GL) * STRIDE];

@@ -1,0 +1,45 @@
+"""The ways a solve's inner steps are split over lanes and waves change no bit
+of any output: each split is compared with the one-lane group (or the other
+split) on the same instances, at horizons around the chunk edges."""
+import numpy as np
+import pytest
+
+from paper_2602_19699_amd import inputs as I
+
+from gpu_helpers import gpu_solve
+
+pytestmark = pytest.mark.gpu
+
+PM, P3 = I.SYS_POINT_MASS, I.SYS_PLANAR3
+FIELDS = ("X", "U", "J", "iters", "status", "Vbar", "Vx", "xK", "cost_trace", "work", "jtrace")
+EDGES = np.array([1, 2, 3, 15, 16, 17, 31, 32, 33, 47, 7, 1, 16], np.int32)
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    from paper_2602_19699_amd import cbic
+    assert torch.cuda.is_available()
+    c = cbic.Context(0)
+    yield c
+    c.close()
+
+
+def _equal(a, b, fields=FIELDS, what=""):
+    for k in fields:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=f"{what} field {k}")
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("form", [{}, {"u_max": 4.0}, {"regularization": 1}], ids=["clip", "bound", "lm"])
+def test_arm_column_lanes_match_one_lane(ctx, prec, form):
+    # 16 lanes: a lane per column of the Riccati step; 1 lane: the whole step.
+    # A non-finite instance and an odd batch (a part-filled last wave) ride along.
+    p, x0 = I.planar3_params(0), I.planar3_x0(len(EDGES), 77)
+    x0[5, 4] = np.nan
+    o = dict(T=EDGES, precision=prec, max_iter=8, trace=True, **form)
+    ref = gpu_solve(ctx, P3, p, x0, 47, group_lanes=1, **o)
+    got = gpu_solve(ctx, P3, p, x0, 47, group_lanes=16, **o)
+    # the work counters count what the lanes of a group read and write together
+    _equal(ref, got, [k for k in FIELDS if k != "work"], f"{form}")
+    np.testing.assert_array_equal(ref["work"][:, 0], got["work"][:, 0])
