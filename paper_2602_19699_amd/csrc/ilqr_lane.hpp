@@ -1425,17 +1425,19 @@ struct Lane {
   // With BOX the trial's controls are clamped into [-umax, umax] (eq. 1).
   // REPLAY rolls out a step whose cost is already known only to write it:
   // the same controls and states, no costs (returns 0).
+  // A lane without a trial in this round (`run` false) only loads its share
+  // of the records; its J_hat is NaN and its step count 0.
   template <int GL, bool BOX, bool REPLAY = false>
   __device__ static double trial(const Model& mdl, const LaneState<R>& w, int s, int T, int buf, int nb,
-                                 R alpha, double Jcur, bool write, int& steps, R* ring, int r, int gbase,
+                                 R alpha, double Jcur, bool run, bool write, int& steps, R* ring, int r, int gbase,
                                  R umax) {
     constexpr int CT = GL * PT;
     const unsigned long long gmask = (GL >= 64) ? ~0ull : ((1ull << GL) - 1ull);
     R xh[N];
     ld(xh, xp(w, buf, 0, s));
     double Jh = 0.0;
-    bool live = true;
-    steps = T;
+    bool live = run;
+    steps = run ? T : 0;
     R nxt[PT][SW];
 #pragma unroll
     for (int q = 0; q < PT; ++q) {
@@ -1506,7 +1508,7 @@ struct Lane {
     }
     if constexpr (!REPLAY)
       if (live) Jh += double(mdl.term(xh));
-    return Jh;
+    return run ? Jh : __builtin_nan("");
   }
 };
 
@@ -1639,27 +1641,30 @@ __device__ __forceinline__ void final_group(const double* __restrict__ prm, cons
 // Up to `iters` iterations for every active slot, with GL lanes per instance.
 // The GL lanes of a group run the backward sweep redundantly (identical
 // arithmetic on identical data; the point mass splits each step over lane
-// pairs by axis, and lanes holding the same gains all store them) and split
-// the line search: in round q lane r tries alpha_j, j = q*GL + r.  The first
-// j whose J_hat < J is taken (a wave ballot over the group), which is exactly
-// the sequential rule.  Systems with their own trial buffers have every lane
-// write its trial and the accepted lane's buffer becomes the iterate; the
-// others write alpha = 1 while trying it and roll another accepted step out
-// once more to write it.  `slots` (optional) maps the group index to a slot,
-// for sparse slot sets.
+// pairs by axis, the arm over lane pairs or, with 16 lanes, by column, and
+// lanes holding the same gains all store them) and the first TW of them split
+// the line search: in round q lane r < TW tries alpha_j, j = q*TW + r.  The
+// first j whose J_hat < J is taken (a wave ballot over the group), which is
+// exactly the sequential rule.  Systems with their own trial buffers have
+// every trial lane write its trial and the accepted lane's buffer becomes the
+// iterate; the others write alpha = 1 while trying it and roll another
+// accepted step out once more to write it.  The work counters count rounds of
+// TW trials.  `slots` (optional) maps the group index to a slot, for sparse
+// slot sets.
 //
 // BOX selects the variant with the control bound of eq. 1 (sp.umax finite).
 //
 // FIN: the launch is the solve's last, and each group finalises its slot
 // (final_group) as soon as it has stopped iterating, while other groups still
 // iterate; every slot of the list is finalised, frozen ones included.
-template <class Sys, class R, int GL, bool BOX, bool FIN = false>
+template <class Sys, class R, int GL, int TW, bool BOX, bool FIN = false>
 __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ prm, LaneState<R> w,
                                                    int nslots, const int32_t* __restrict__ slots,
                                                    SolveParams sp, int iters_this_launch, IterTrace tr,
                                                    int Tmax = 0, int lookahead = 0, FinalOut fo = {}) {
   using LN = Lane<Sys, R>;
   static_assert(GL >= 1 && GL <= 16 && (GL & (GL - 1)) == 0, "group width must be a power of two <= 16");
+  static_assert(TW >= 1 && TW <= GL && (TW & (TW - 1)) == 0, "trials per round: a power of two <= the group width");
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int gi = tid / GL;
   const int r = tid & (GL - 1);
@@ -1725,16 +1730,14 @@ __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ pr
         // the iterate (no second rollout); one call site of the rollout keeps the
         // register footprint down
         const int wb = (buf + 1 + r) % w.nbuf;  // never the iterate's buffer (GL < nbuf)
-        for (int j0 = 0; j0 < sp.ls_trials && acc < 0; j0 += GL) {
+        for (int j0 = 0; j0 < sp.ls_trials && acc < 0; j0 += TW) {
           const int j = j0 + r;
-          double Jh = __builtin_nan("");
+          const bool run = r < TW && j < sp.ls_trials;
           int steps = 0;
-          if (j < sp.ls_trials) {
-            double alpha = 1.0;
-            for (int q = 0; q < j; ++q) alpha *= sp.beta;
-            Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, wb, R(alpha), J, true, steps, stage, r, gbase,
-                                             R(sp.umax));
-          }
+          double alpha = 1.0;
+          for (int q = 0; q < j; ++q) alpha *= sp.beta;
+          const double Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, wb, R(alpha), J, run, run, steps, stage,
+                                                        r, gbase, R(sp.umax));
           ++npass;
           // every lane writes what it rolled out; the lanes of a group read the
           // same data, so a round reads as many steps as its longest trial
@@ -1763,21 +1766,23 @@ __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ pr
         // (its J_hat is known from the round)
         for (int j0 = 0;;) {
           const int j = j0 + r;
-          double Jh = __builtin_nan("");
+          const bool run = r < TW && j < sp.ls_trials;
           int steps = 0;
-          if (j < sp.ls_trials) {
+          double Jh = __builtin_nan("");
+          // (uniform over the group: some lane runs)
+          if (j0 < sp.ls_trials) {
             double alpha = 1.0;
             for (int q = 0; q < j; ++q) alpha *= sp.beta;
             // alpha = 1 (j == 0) is written while it runs, as is every trial
-            // of a one-lane group
-            Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, buf ^ 1, R(alpha), J, j == 0 || GL == 1, steps,
-                                             stage, r, gbase, R(sp.umax));
+            // of a round of one
+            Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, buf ^ 1, R(alpha), J, run, run && (j == 0 || TW == 1),
+                                             steps, stage, r, gbase, R(sp.umax));
           }
           ++npass;
           // the lanes of a group read the same data: a round moves as many steps
           // as its longest trial; only the alpha = 1 trial (or every trial of a
-          // one-lane group) writes
-          if (j0 == 0 || GL == 1) nwrite += (GL == 1) ? steps : __shfl(steps, gbase, 64);
+          // round of one) writes
+          if (j0 == 0 || TW == 1) nwrite += (GL == 1) ? steps : __shfl(steps, gbase, 64);
           int longest = steps;
 #pragma unroll
           for (int o = 1; o < GL; o <<= 1) longest = max(longest, __shfl_xor(longest, o, 64));
@@ -1790,15 +1795,15 @@ __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ pr
             acc = j0 + rs;
             Jn = __shfl(Jh, gbase + rs, 64);
           }
-          j0 += GL;
-          if (acc == 0 || (acc > 0 && GL == 1) || (acc < 0 && j0 >= sp.ls_trials)) break;
+          j0 += TW;
+          if (acc == 0 || (acc > 0 && TW == 1) || (acc < 0 && j0 >= sp.ls_trials)) break;
           if (acc > 0) {
             // the group's lead lane writes the replay
             double alpha = 1.0;
             for (int q = 0; q < acc; ++q) alpha *= sp.beta;
             int rs = 0;
-            LN::template trial<GL, BOX, true>(mdl, w, s, T, buf, buf ^ 1, R(alpha), __builtin_inf(), lead, rs,
-                                              stage, r, gbase, R(sp.umax));
+            LN::template trial<GL, BOX, true>(mdl, w, s, T, buf, buf ^ 1, R(alpha), __builtin_inf(), true, lead,
+                                              rs, stage, r, gbase, R(sp.umax));
             ++npass;
             nread += rs;
             nwrite += rs;

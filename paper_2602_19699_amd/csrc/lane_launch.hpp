@@ -82,16 +82,16 @@ struct LaneLaunch {
   // the bounded variant (eq. 1) is a kernel of its own, so that the
   // unbounded one keeps its register allocation; FIN finalises in the same
   // kernel (fo, Tmax, lookahead)
-  template <int GL, bool FIN>
+  template <int GL, int TW, bool FIN>
   static hipError_t iterate_g(const double* prm, const LaneState<R>& w, int nthreads, const int32_t* slots,
                               const SolveParams& sp, int G, const IterTrace& tr, int Tmax, int lookahead,
                               const FinalOut& fo, hipStream_t st) {
     const long total = long(nthreads) * GL;
     if (__builtin_isfinite(sp.umax))
-      hipLaunchKernelGGL((lane_iterate<Sys, R, GL, true, FIN>), dim3((total + WG - 1) / WG), dim3(WG), 0, st, prm,
+      hipLaunchKernelGGL((lane_iterate<Sys, R, GL, TW, true, FIN>), dim3((total + WG - 1) / WG), dim3(WG), 0, st, prm,
                          w, nthreads, slots, sp, G, tr, Tmax, lookahead, fo);
     else
-      hipLaunchKernelGGL((lane_iterate<Sys, R, GL, false, FIN>), dim3((total + WG - 1) / WG), dim3(WG), 0, st,
+      hipLaunchKernelGGL((lane_iterate<Sys, R, GL, TW, false, FIN>), dim3((total + WG - 1) / WG), dim3(WG), 0, st,
                          prm, w, nthreads, slots, sp, G, tr, Tmax, lookahead, fo);
     return hipGetLastError();
   }
@@ -103,14 +103,31 @@ struct LaneLaunch {
     if (nthreads <= 0) return hipSuccess;
     auto w = lane_state<R>(base, N, M, Bcap, Tcap, lane_bufs<Sys>());
     const SolveParams d = to_dev(sp);
+#define CBIC_G(GL, TW) iterate_g<GL, TW, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st)
+    // lanes per instance and, where fewer, trials per line-search round
+    // (group_code)
     switch (group) {
-      case 1: return iterate_g<1, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st);
-      case 2: return iterate_g<2, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st);
-      case 4: return iterate_g<4, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st);
-      case 8: return iterate_g<8, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st);
-      case 16: return iterate_g<16, FIN>(prm, w, nthreads, slots, d, G, tr, Tmax, lookahead, fo, st);
-      default: return hipErrorInvalidValue;
+      case 1: return CBIC_G(1, 1);
+      case 2: return CBIC_G(2, 2);
+      case 4: return CBIC_G(4, 4);
+      case 8: return CBIC_G(8, 8);
+      case 16: return CBIC_G(16, 16);
+      default: break;
     }
+    if constexpr (Sys::template kWideLanes<R>() > 0) {
+      switch (group) {
+        case group_code(8, 1): return CBIC_G(8, 1);
+        case group_code(8, 2): return CBIC_G(8, 2);
+        case group_code(8, 4): return CBIC_G(8, 4);
+        case group_code(16, 8): return CBIC_G(16, 8);
+        default: break;
+      }
+      if constexpr (Sys::template kWideLanes<R>() > 131072) {
+        if (group == group_code(16, 4)) return CBIC_G(16, 4);
+      }
+    }
+#undef CBIC_G
+    return hipErrorInvalidValue;
   }
 
   static hipError_t iterate(const double* prm, void* base, int Bcap, int Tcap, int nthreads,
@@ -143,7 +160,7 @@ struct LaneLaunch {
 
   static const Launcher* get() {
     static const Launcher L{N,         M,       int(sizeof(R)), CBIC_SCHED_LANE, &ws_bytes, &init, &iterate,
-                            &finalize, 0,       lane_bufs<Sys>(), &iterate_final};
+                            &finalize, 0,       lane_bufs<Sys>(), &iterate_final,  Sys::template kWideLanes<R>()};
     return &L;
   }
 };

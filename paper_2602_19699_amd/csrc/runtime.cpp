@@ -74,11 +74,25 @@ int cu_count(int device) {
   return v;
 }
 
-int default_group(int schedule, int B, int precision, int device) {
-  if (schedule == CBIC_SCHED_GROUP) return (precision == CBIC_FP64 || B <= cu_count(device)) ? 1 : 2;
-  int g = 1;
-  while (g < 16 && long(B) * g * 2 <= 65536) g *= 2;
-  return g;
+// Lane schedule: a line-search round tries as many steps as fill the chip's
+// SIMDs once (65536 lanes), for every instance.  The other work of a group,
+// the derivative blocks and the arm's columns, shares out over more lanes than
+// that, so the groups are wider: 16 lanes up to wide_lanes (two waves per
+// SIMD, four for the arm in FP32), 8 beyond.  Measured (solve, us, 4 / 8 / 16
+// lanes): point mass, mixed, tol 1e-4: B 8192 662 / 509 / 455, B 16384 667 /
+// 538 / 732, B 32768 941 / 916 / 1290 (2 lanes 1293); FP64: B 8192 1310 / 997 /
+// 943, B 16384 1373 / 1140 / 1510; arm (8 / 16 lanes), mixed: B 8192 12035 /
+// 8539, B 16384 13778 / 13056, B 32768 21678 / 22801; FP64: B 8192 20740 /
+// 18639, B 12000 23553 / 26431.  The linear-quadratic kernels have nothing to
+// share and are slower in wider groups (6 states, FP64, B 16384: 4 / 8 lanes
+// 2176 / 3090).
+int default_group(const Launcher* L, int B, int precision, int device) {
+  if (L->schedule == CBIC_SCHED_GROUP) return (precision == CBIC_FP64 || B <= cu_count(device)) ? 1 : 2;
+  int trials = 1;
+  while (trials < 16 && long(B) * trials * 2 <= 65536) trials *= 2;
+  if (L->wide_lanes == 0) return trials;
+  const int lanes = long(B) * 16 <= L->wide_lanes ? 16 : 8;
+  return group_code(lanes > trials ? lanes : trials, trials);
 }
 
 int requested_group(const Launcher* L, const cbic_solve_opts* o) {

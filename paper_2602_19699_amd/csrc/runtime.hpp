@@ -85,6 +85,9 @@ struct Launcher {
   hipError_t (*iterate_final)(const double* prm, void* base, int Bcap, int Tcap, int nthreads,
                               const int32_t* slots, const SolveParamsH& sp, int G, int group, const IterTrace& tr,
                               int Tmax, int lookahead, const FinalOutH& o, hipStream_t st) = nullptr;
+  // lanes of a batch up to which its groups widen to 16 lanes (0: the groups
+  // are as wide as the line-search rounds)
+  int wide_lanes = 0;
 };
 
 const Launcher* find_launcher(int kind, int n, int m, int precision, int schedule);
@@ -95,12 +98,15 @@ cbic_status check_solve_opts(const cbic_solve_opts* o);
 // variant clips nothing: eps is then negative)
 SolveParamsH solve_params(const cbic_solve_opts* o);
 
+// a lane-schedule choice as one number: the lanes per instance, and the
+// trials per line-search round where they are fewer (0 above: as many)
+constexpr int group_code(int lanes, int trials) { return lanes | (trials == lanes ? 0 : trials << 8); }
 // the schedule choice when the caller leaves it to the library: lanes per
-// instance of the lane schedule (enough groups to give every SIMD of the chip
-// a wave or two), instances per compute unit of the workgroup schedule (one
+// instance and trials per line-search round of the lane schedule (see
+// runtime.cpp), instances per compute unit of the workgroup schedule (one
 // while the batch fits the device's compute units one instance each, two
 // above; always one in FP64)
-int default_group(int schedule, int B, int precision, int device);
+int default_group(const Launcher* L, int B, int precision, int device);
 // the caller's own choice for the launcher's schedule (0: none)
 int requested_group(const Launcher* L, const cbic_solve_opts* o);
 // compute units of a device (cached)

@@ -43,3 +43,28 @@ def test_arm_column_lanes_match_one_lane(ctx, prec, form):
     # the work counters count what the lanes of a group read and write together
     _equal(ref, got, [k for k in FIELDS if k != "work"], f"{form}")
     np.testing.assert_array_equal(ref["work"][:, 0], got["work"][:, 0])
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("kind", [PM, P3], ids=["pm", "arm"])
+@pytest.mark.parametrize("B,trials", [(4097, 8), (8193, 4), (16385, 2), (32769, 1)])
+def test_default_widths_match_narrow_groups(ctx, kind, prec, B, trials):
+    # the library's own choice of lanes for a large batch keeps that batch's
+    # line-search rounds: every output and the work counters equal those of a
+    # group as wide as its rounds
+    p = I.point_mass_params(0) if kind == PM else I.planar3_params(0)
+    x0 = I.point_mass_x0(B, 5) if kind == PM else I.planar3_x0(B, 5)
+    o = dict(T=I.horizons(B, 1, 19, 6), precision=prec, max_iter=3, trace=True)
+    _equal(gpu_solve(ctx, kind, p, x0, 19, group_lanes=trials, **o), gpu_solve(ctx, kind, p, x0, 19, **o))
+
+
+@pytest.mark.parametrize("kind", [PM, P3], ids=["pm", "arm"])
+@pytest.mark.parametrize("trials", [1, 3, 5, 11])
+def test_trial_budget_of_any_size(ctx, kind, trials):
+    # a last line-search round with fewer trials than lanes
+    p = I.point_mass_params(0) if kind == PM else I.planar3_params(0)
+    x0 = I.point_mass_x0(40, 5) if kind == PM else I.planar3_x0(40, 5)
+    o = dict(T=I.horizons(40, 1, 50, 6), max_iter=6, ls_max_trials=trials, trace=True)
+    ref = gpu_solve(ctx, kind, p, x0, 50, group_lanes=1, **o)
+    for g in (2, 4, 8, 16):
+        _equal(ref, gpu_solve(ctx, kind, p, x0, 50, group_lanes=g, **o), [k for k in FIELDS if k != "work"], f"{g}")
