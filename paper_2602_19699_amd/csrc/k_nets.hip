@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(kNetWG) mlp_score(MlpDev net, MlpLds L, int B,
   const bool valid = b < B;
   const double* xb = x + size_t(valid ? b : 0) * n;
   const float tau = (T && valid) ? float(Tmax - T[b]) * (1.0f / float(Tmax)) : 0.0f;
-  const nf4 y = mlp_tile<W, 0, ACT>(net, L, lds, [&](int s, int g) {
+  const nf4 y = mlp_tile<W, ACT>(net, L, lds, [&](int s, int g) {
     const int f = 4 * s + g;
     return !valid ? 0.0f : (f < n ? float(xb[f]) : (f == n && T ? tau : 0.0f));
   });
@@ -65,7 +65,7 @@ __global__ void __launch_bounds__(kNetWG) mlp_rows(MlpDev net, MlpLds L, int B, 
   const int b = (blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6)) * 16 + (lane & 15);
   const bool valid = b < B;
   const float* ib = in + size_t(valid ? b : 0) * net.in_dim;
-  const nf4 y = mlp_tile<W, 0, ACT>(net, L, lds, [&](int s, int gg) {
+  const nf4 y = mlp_tile<W, ACT>(net, L, lds, [&](int s, int gg) {
     const int f = 4 * s + gg;
     return valid && f < net.in_dim ? ib[f] : 0.0f;
   });
@@ -73,6 +73,69 @@ __global__ void __launch_bounds__(kNetWG) mlp_rows(MlpDev net, MlpLds L, int B, 
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (4 * g + r < net.out_dim) out[size_t(b) * net.out_dim + 4 * g + r] = y[r];
+}
+
+// mlp_score and mlp_rows with the weights in registers (MlpRegs), for networks
+// of one or two hidden layers and 5..8 inputs: a wave loads them once and
+// takes every nwaves-th tile of 16 samples.  Bound by issue: 88 MFMA of 32
+// cycles and about 340 vector instructions (half of them the activations) per
+// tile of a 64-64 network.  163840 candidates: 27 us (68 TFLOP/s with the
+// padding), 47 us with the weights staged in LDS by every workgroup of four
+// tiles; 3000 candidates 5.6 us against 13.6.
+template <int W, int ACT, int DEPTH>
+__global__ void __launch_bounds__(kNetWG, 3) mlp_score_r(MlpDev net, int B, int n, const double* __restrict__ x,
+                                                         const int32_t* __restrict__ T, int Tmax,
+                                                         float* __restrict__ score) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int nwaves = gridDim.x * (kNetWG / 64);
+  MlpRegs<W, DEPTH> w;
+  w.load(net, lane);
+  const float inv_T = 1.0f / float(Tmax);
+  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile * 16 < B; tile += nwaves) {
+    const int b = tile * 16 + c;
+    const bool valid = b < B;
+    const double* xb = x + size_t(valid ? b : 0) * n;
+    const float tau = (T && valid) ? float(Tmax - T[b]) * inv_T : 0.0f;
+    float f[kRegIn4 / 4];
+#pragma unroll
+    for (int s = 0; s < kRegIn4 / 4; ++s) {
+      const int i = 4 * s + g;
+      f[s] = !valid ? 0.0f : (i < n ? float(xb[i]) : (i == n && T ? tau : 0.0f));
+    }
+    const nf4 y = w.template eval<ACT>(f, net.out_act, net.out_scale);
+    if (valid && lane < 16) score[b] = y[0];
+  }
+}
+
+template <int W, int ACT, int DEPTH>
+__global__ void __launch_bounds__(kNetWG, 3) mlp_rows_r(MlpDev net, int B, const float* __restrict__ in,
+                                                        float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int nwaves = gridDim.x * (kNetWG / 64);
+  MlpRegs<W, DEPTH> w;
+  w.load(net, lane);
+  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile * 16 < B; tile += nwaves) {
+    const int b = tile * 16 + c;
+    const bool valid = b < B;
+    const float* ib = in + size_t(valid ? b : 0) * net.in_dim;
+    float f[kRegIn4 / 4];
+#pragma unroll
+    for (int s = 0; s < kRegIn4 / 4; ++s) f[s] = valid && 4 * s + g < net.in_dim ? ib[4 * s + g] : 0.0f;
+    const nf4 y = w.template eval<ACT>(f, net.out_act, net.out_scale);
+    if (valid)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * g + r < net.out_dim) out[size_t(b) * net.out_dim + 4 * g + r] = y[r];
+  }
+}
+
+// whether the register kernels take a network: their loops are unrolled for
+// eight padded inputs, and a third hidden layer would leave one wave per SIMD
+bool regs_take(const MlpDev& d) { return (d.in_dim + 3) / 4 * 4 == kRegIn4 && d.depth <= 2; }
+// blocks for B samples: three waves per SIMD at most, then several tiles a wave
+int reg_blocks(int B, int device) {
+  const int want = (B + kNetWG / 4 - 1) / (kNetWG / 4), most = 3 * cu_count(device);
+  return want < most ? want : most;
 }
 
 // ------------------------------------------------------------------ selection
@@ -287,37 +350,91 @@ __global__ void __launch_bounds__(kSelWG) sel_scatter(const float* __restrict__ 
 }
 
 // ------------------------------------------------------------------ actor rollout
-// 16 instances per wave, four lanes per instance: the lanes of an instance
-// keep its state and step the FP64 dynamics redundantly, and the wave
-// evaluates u_k = actor(x_k, tau_k) for its 16 instances on the matrix cores.
-// The wave runs until its longest horizon, so ragged batches are taken in
-// horizon order (perm, longest first) and a wave holds similar horizons.
-// Outputs are zero past each horizon (all zero for a horizon outside
-// 1..T_max).
+// Sixteen instances per workgroup of W / 16 waves: wave v evaluates the
+// neurons 16 v .. 16 v + 15 of every hidden layer for all sixteen and keeps
+// those weights in registers; a layer's activations pass through LDS.  One
+// wave (another one from block to block) also evaluates the output layer,
+// keeps the instances' states (four lanes per instance, redundantly), steps
+// the FP64 dynamics and publishes the next inputs.  The block runs until its
+// longest horizon, so ragged batches are taken in horizon order (perm, longest
+// first) and a block holds similar horizons.  Outputs are zero past each
+// horizon (all zero for a horizon outside 1..T_max).
+//
+// Bound: the serial chain of one step (the matrix products of the layers, 16
+// dependent MFMA each, the activations between them and the dynamics), which
+// the split over waves shortens to a quarter of its products and activations;
+// the products are those of one wave evaluating the network alone, in the same
+// order.  64-64 network, horizons up to 100: a step alone takes 0.87 us (2.0 us
+// with one wave per 16 instances and the weights read from LDS every step);
+// 16384 point-mass instances, horizons 1..100: 172 us against 278.
 template <class Sys, int W, int ACT>
-__global__ void __launch_bounds__(kNetWG) actor_rollout(const double* __restrict__ prm, MlpDev net, MlpLds L, int B,
-                                                        int Tmax, const int32_t* __restrict__ Tin,
-                                                        const int32_t* __restrict__ perm,
-                                                        const double* __restrict__ x0, double* __restrict__ U,
-                                                        double* __restrict__ X) {
+__global__ void __launch_bounds__(4 * W) actor_rollout(const double* __restrict__ prm, MlpDev net, int B, int Tmax,
+                                                       const int32_t* __restrict__ Tin,
+                                                       const int32_t* __restrict__ perm,
+                                                       const double* __restrict__ x0, double* __restrict__ U,
+                                                       double* __restrict__ X) {
   constexpr int N = Sys::N, M = Sys::M;
   constexpr int IN4 = (N + 1 + 3) & ~3;
+  constexpr int NW = W / 16, KS = W / 4, HL = 3;  // waves, K steps of a hidden layer, hidden layers beyond the first
   static_assert(M <= 4, "outputs of lane group 0");
-  extern __shared__ float lds[];
-  mlp_stage(net, L, lds);
-  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-  const int slot = (blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6)) * 16 + c;
+  __shared__ nf4 hb[2][NW][64];
+  __shared__ float feat[IN4][16];
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15, wv = threadIdx.x >> 6;
+  // blocks 256 apart share a compute unit, whose SIMDs take a wave of each: the
+  // leads, with the output layer and the dynamics on top, go to different ones
+  const bool lead = wv == int(blockIdx.x + blockIdx.x / 256) % NW;
+  // this wave's weights: neuron 16 wv + c (output c for the output layer) by
+  // the K rows of lane group g
+  float w0[IN4 / 4], wh[HL][KS], wo[KS];
+  nf4 b0, bh[HL], bo;
+  {
+    const int in = net.in_dim, out = net.out_dim;
+    const float* p = net.p;
+#pragma unroll
+    for (int s = 0; s < IN4 / 4; ++s) w0[s] = 4 * s + g < in ? p[(4 * s + g) * W + 16 * wv + c] : 0.0f;
+    p += in * W;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) b0[r] = p[16 * wv + 4 * g + r];
+    p += W;
+#pragma unroll
+    for (int l = 0; l < HL; ++l)
+      if (l + 1 < net.depth) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) wh[l][s] = p[(16 * (s >> 2) + 4 * g + (s & 3)) * W + 16 * wv + c];
+        p += W * W;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bh[l][r] = p[16 * wv + 4 * g + r];
+        p += W;
+      }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) wo[s] = c < out ? p[(16 * (s >> 2) + 4 * g + (s & 3)) * out + c] : 0.0f;
+    p += W * out;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bo[r] = 4 * g + r < out ? p[4 * g + r] : 0.0f;
+  }
+  const int slot = blockIdx.x * 16 + c;
   const bool valid = slot < B;
   const int b = valid ? (perm ? perm[slot] : slot) : 0;
   const typename Sys::template Model<double> mdl{prm};
   const int Tr = valid ? (Tin ? Tin[b] : Tmax) : 0;
   const int T = (Tr < 1 || Tr > Tmax) ? 0 : Tr;
-  int Tw = T;
+  int Tw = T;  // the block's longest horizon (every wave holds the same sixteen)
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) Tw = max(Tw, __shfl_xor(Tw, o, 64));
-  const bool writer = valid && g == 0;
-  double* Ub = U + size_t(valid ? b : 0) * Tmax * M;
-  double* Xb = X ? X + size_t(valid ? b : 0) * (Tmax + 1) * N : nullptr;
+  for (int o = 8; o >= 1; o >>= 1) Tw = max(Tw, __shfl_xor(Tw, o, 64));
+  // zeros past the horizons, a wave per instance
+  for (int i = wv; i < 16; i += NW) {
+    if (int(blockIdx.x) * 16 + i >= B) break;
+    const int bi = __shfl(b, i, 64), Ti = __shfl(T, i, 64);
+    double* u = U + size_t(bi) * Tmax * M;
+    for (int q = Ti * M + lane; q < Tmax * M; q += 64) u[q] = 0.0;
+    if (X) {
+      double* xx = X + size_t(bi) * (Tmax + 1) * N;
+      for (int q = (Ti + 1) * N + lane; q < (Tmax + 1) * N; q += 64) xx[q] = 0.0;
+    }
+  }
+  const bool writer = lead && valid && g == 0;
+  double* Ub = U + size_t(b) * Tmax * M;
+  double* Xb = X ? X + size_t(b) * (Tmax + 1) * N : nullptr;
   double x[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) x[i] = T > 0 ? x0[size_t(b) * N + i] : 0.0;
@@ -325,59 +442,86 @@ __global__ void __launch_bounds__(kNetWG) actor_rollout(const double* __restrict
 #pragma unroll
     for (int i = 0; i < N; ++i) Xb[i] = x[i];
   const float inv_T = 1.0f / float(Tmax);
-  for (int k = 0; k < Tw; ++k) {
-    float f[IN4];
+  // the inputs of step k: lane group g publishes features g, g + 4, ...
+  auto publish = [&](int k) {
 #pragma unroll
-    for (int i = 0; i < IN4; ++i) f[i] = i < N ? float(x[i < N ? i : 0]) : (i == N ? float(Tmax - T + k) * inv_T : 0.0f);
-    const nf4 y = mlp_tile<W, IN4, ACT>(net, L, lds, [&](int s, int gg) {
-      return gg == 0 ? f[4 * s] : (gg == 1 ? f[4 * s + 1] : (gg == 2 ? f[4 * s + 2] : f[4 * s + 3]));
-    });
-    // outputs 0..M-1 of instance c sit in lane c (group 0), registers 0..M-1
-    double u[M];
+    for (int s = 0; s < IN4 / 4; ++s) {
+      float f[4];
 #pragma unroll
-    for (int o = 0; o < M; ++o) u[o] = double(__shfl(y[o], c, 64));
-    if (k < T) {
-      double xn[N];
-      mdl.dyn(x, u, xn);
-#pragma unroll
-      for (int i = 0; i < N; ++i) x[i] = xn[i];
-      if (writer) {
-#pragma unroll
-        for (int i = 0; i < M; ++i) Ub[size_t(k) * M + i] = u[i];
-        if (Xb)
-#pragma unroll
-          for (int i = 0; i < N; ++i) Xb[size_t(k + 1) * N + i] = x[i];
+      for (int q = 0; q < 4; ++q) {
+        const int i = 4 * s + q;
+        f[q] = i < N ? float(x[i < N ? i : 0]) : (i == N ? float(Tmax - T + k) * inv_T : 0.0f);
       }
+      feat[4 * s + g][c] = g == 0 ? f[0] : (g == 1 ? f[1] : (g == 2 ? f[2] : f[3]));
     }
-  }
-  if (writer) {
-    for (int k = T; k < Tmax; ++k)
+  };
+  if (lead) publish(0);
+  __syncthreads();
+  for (int k = 0; k < Tw; ++k) {
+    nf4 h = b0;
 #pragma unroll
-      for (int i = 0; i < M; ++i) Ub[size_t(k) * M + i] = 0.0;
-    if (Xb)
-      for (int k = T + 1; k <= Tmax; ++k)
+    for (int s = 0; s < IN4 / 4; ++s) h = mfma_f32_16x16x4(w0[s], feat[4 * s + g][c], h);
 #pragma unroll
-        for (int i = 0; i < N; ++i) Xb[size_t(k) * N + i] = 0.0;
+    for (int r = 0; r < 4; ++r) h[r] = mlp_act<ACT>(h[r]);
+    hb[0][wv][lane] = h;
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < HL; ++l)
+      if (l + 1 < net.depth) {
+        nf4 o = bh[l], hin[NW];
+#pragma unroll
+        for (int t = 0; t < NW; ++t) hin[t] = hb[l & 1][t][lane];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) o = mfma_f32_16x16x4(wh[l][s], hin[s >> 2][s & 3], o);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = mlp_act<ACT>(o[r]);
+        hb[(l + 1) & 1][wv][lane] = o;
+        __syncthreads();
+      }
+    if (lead) {
+      nf4 y = bo, hin[NW];
+#pragma unroll
+      for (int t = 0; t < NW; ++t) hin[t] = hb[(net.depth - 1) & 1][t][lane];
+#pragma unroll
+      for (int s = 0; s < KS; ++s) y = mfma_f32_16x16x4(wo[s], hin[s >> 2][s & 3], y);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y[r] = mlp_out(y[r], net.out_act, net.out_scale);
+      // outputs 0..M-1 of instance c sit in lane c (group 0), registers 0..M-1
+      double u[M];
+#pragma unroll
+      for (int o = 0; o < M; ++o) u[o] = double(__shfl(y[o], c, 64));
+      if (k < T) {
+        double xn[N];
+        mdl.dyn(x, u, xn);
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = xn[i];
+        if (writer) {
+#pragma unroll
+          for (int i = 0; i < M; ++i) Ub[size_t(k) * M + i] = u[i];
+          if (Xb)
+#pragma unroll
+            for (int i = 0; i < N; ++i) Xb[size_t(k + 1) * N + i] = x[i];
+        }
+      }
+      publish(k + 1);
+    }
+    __syncthreads();
   }
 }
 
 template <class Sys, int W, int ACT>
-hipError_t launch_actor_k(const double* prm, const MlpDev& net, const MlpLds& L, int B, int Tmax,
-                          const int32_t* d_T, const int32_t* perm, const double* x0, double* U, double* X,
-                          hipStream_t st) {
-  const dim3 grid((B + kNetWG / 4 - 1) / (kNetWG / 4)), block(kNetWG);
-  const size_t lds = size_t(L.total()) * sizeof(float);
-  hipError_t e = allow_lds(actor_rollout<Sys, W, ACT>, lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), grid, block, lds, st, prm, net, L, B, Tmax, d_T, perm, x0, U, X);
+hipError_t launch_actor_k(const double* prm, const MlpDev& net, int B, int Tmax, const int32_t* d_T,
+                          const int32_t* perm, const double* x0, double* U, double* X, hipStream_t st) {
+  hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), dim3((B + 15) / 16), dim3(4 * W), 0, st, prm, net, B, Tmax, d_T,
+                     perm, x0, U, X);
   return hipGetLastError();
 }
 
 template <class Sys>
-hipError_t launch_actor(const double* prm, const MlpDev& net, const MlpLds& L, int B, int Tmax, const int32_t* d_T,
+hipError_t launch_actor(const double* prm, const MlpDev& net, int W, int B, int Tmax, const int32_t* d_T,
                         const int32_t* perm, const double* x0, double* U, double* X, hipStream_t st) {
-#define CBIC_ACTOR(WW, AA) launch_actor_k<Sys, WW, AA>(prm, net, L, B, Tmax, d_T, perm, x0, U, X, st)
-  if (L.W == 32) return net.act == 0 ? CBIC_ACTOR(32, 0) : (net.act == 1 ? CBIC_ACTOR(32, 1) : CBIC_ACTOR(32, 2));
+#define CBIC_ACTOR(WW, AA) launch_actor_k<Sys, WW, AA>(prm, net, B, Tmax, d_T, perm, x0, U, X, st)
+  if (W == 32) return net.act == 0 ? CBIC_ACTOR(32, 0) : (net.act == 1 ? CBIC_ACTOR(32, 1) : CBIC_ACTOR(32, 2));
   return net.act == 0 ? CBIC_ACTOR(64, 0) : (net.act == 1 ? CBIC_ACTOR(64, 1) : CBIC_ACTOR(64, 2));
 #undef CBIC_ACTOR
 }
@@ -436,12 +580,17 @@ cbic_status cbic_mlp_forward(cbic_context* ctx, const cbic_mlp* net, int32_t B, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*net);
   const MlpLds L = mlp_lds(net->in_dim, net->width, net->depth, net->out_dim);
-  const dim3 grid((B + kNetWG / 4 - 1) / (kNetWG / 4)), block(kNetWG);
+  const dim3 grid((B + kNetWG / 4 - 1) / (kNetWG / 4)), rgrid(reg_blocks(B, ctx->device)), block(kNetWG);
+  const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
-#define CBIC_ROWS(WW, AA)                                                                  \
-  do {                                                                                     \
-    HIP_TRY(allow_lds(mlp_rows<WW, AA>, lds));                                             \
-    hipLaunchKernelGGL((mlp_rows<WW, AA>), grid, block, lds, st, d, L, B, d_in, d_out);    \
+#define CBIC_ROWS(WW, AA)                                                                                    \
+  do {                                                                                                       \
+    if (regs && d.depth == 1) hipLaunchKernelGGL((mlp_rows_r<WW, AA, 1>), rgrid, block, 0, st, d, B, d_in, d_out); \
+    else if (regs) hipLaunchKernelGGL((mlp_rows_r<WW, AA, 2>), rgrid, block, 0, st, d, B, d_in, d_out);      \
+    else {                                                                                                   \
+      HIP_TRY(allow_lds(mlp_rows<WW, AA>, lds));                                                             \
+      hipLaunchKernelGGL((mlp_rows<WW, AA>), grid, block, lds, st, d, L, B, d_in, d_out);                    \
+    }                                                                                                        \
   } while (0)
   if (net->width == 32) {
     if (net->act == 0) CBIC_ROWS(32, 0);
@@ -476,12 +625,19 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*net);
   const MlpLds L = mlp_lds(net->in_dim, net->width, net->depth, net->out_dim);
-  const dim3 grid((Bc + kNetWG / 4 - 1) / (kNetWG / 4)), block(kNetWG);
+  const dim3 grid((Bc + kNetWG / 4 - 1) / (kNetWG / 4)), rgrid(reg_blocks(Bc, ctx->device)), block(kNetWG);
+  const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
-#define CBIC_SCORE(WW, AA)                                                                           \
-  do {                                                                                               \
-    HIP_TRY(allow_lds(mlp_score<WW, AA>, lds));                                                      \
-    hipLaunchKernelGGL((mlp_score<WW, AA>), grid, block, lds, st, d, L, Bc, n, d_x, d_T, T_max, d_score); \
+#define CBIC_SCORE(WW, AA)                                                                                      \
+  do {                                                                                                          \
+    if (regs && d.depth == 1)                                                                                   \
+      hipLaunchKernelGGL((mlp_score_r<WW, AA, 1>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score);    \
+    else if (regs)                                                                                              \
+      hipLaunchKernelGGL((mlp_score_r<WW, AA, 2>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score);    \
+    else {                                                                                                      \
+      HIP_TRY(allow_lds(mlp_score<WW, AA>, lds));                                                               \
+      hipLaunchKernelGGL((mlp_score<WW, AA>), grid, block, lds, st, d, L, Bc, n, d_x, d_T, T_max, d_score);     \
+    }                                                                                                           \
   } while (0)
   if (net->width == 32) {
     if (net->act == 0) CBIC_SCORE(32, 0);
@@ -536,7 +692,6 @@ cbic_status cbic_actor_rollout(cbic_context* ctx, const cbic_system* sys, const 
   (void)hipGetLastError();  // launch errors below are this call's, not a stale one
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*actor);
-  const MlpLds w = mlp_lds(actor->in_dim, actor->width, actor->depth, actor->out_dim);
   const bool known = sys->kind == CBIC_SYS_POINT_MASS || sys->kind == CBIC_SYS_PLANAR3 ||
                      (sys->kind == CBIC_SYS_LQ && ((sys->n == 2 && sys->m == 1) || (sys->n == 4 && sys->m == 2) ||
                                                    (sys->n == 6 && sys->m == 3)));
@@ -558,15 +713,15 @@ cbic_status cbic_actor_rollout(cbic_context* ctx, const cbic_system* sys, const 
   }
   hipError_t e;
   if (sys->kind == CBIC_SYS_POINT_MASS) {
-    e = launch_actor<PointMass>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<PointMass>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_PLANAR3) {
-    e = launch_actor<Arm3>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<Arm3>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_LQ && sys->n == 2 && sys->m == 1) {
-    e = launch_actor<LinQuad<2, 1>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<2, 1>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_LQ && sys->n == 4 && sys->m == 2) {
-    e = launch_actor<LinQuad<4, 2>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<4, 2>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else {
-    e = launch_actor<LinQuad<6, 3>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<6, 3>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   }
   HIP_TRY(e);
   if (perm) {

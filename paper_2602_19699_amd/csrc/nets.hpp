@@ -107,11 +107,9 @@ __device__ inline void mlp_stage(const MlpDev& net, const MlpLds& L, float* lds)
 }
 
 // The network for the wave's 16 samples.  feat(s, g) returns input feature
-// 4 s + g of this lane's sample (zero past in_dim); IN4 > 0 fixes in4 at
-// compile time (the loop over s is then unrolled, so feat may pick registers
-// with a constant s).  Returns, in lane l, outputs 4 (l / 16) + r (r = 0..3)
-// of sample l % 16 after the output map.
-template <int W, int IN4, int ACT, class Feat>
+// 4 s + g of this lane's sample (zero past in_dim).  Returns, in lane l,
+// outputs 4 (l / 16) + r (r = 0..3) of sample l % 16 after the output map.
+template <int W, int ACT, class Feat>
 __device__ __forceinline__ nf4 mlp_tile(const MlpDev& net, const MlpLds& L, const float* lds, Feat feat) {
   constexpr int NT = W / 16;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
@@ -128,12 +126,7 @@ __device__ __forceinline__ nf4 mlp_tile(const MlpDev& net, const MlpLds& L, cons
 #pragma unroll
       for (int t = 0; t < NT; ++t) h[t] = mfma_f32_16x16x4(row[16 * t], bv, h[t]);
     };
-    if constexpr (IN4 > 0) {
-#pragma unroll
-      for (int s = 0; s < IN4 / 4; ++s) kstep(s);
-    } else {
-      for (int s = 0; s < L.in4 / 4; ++s) kstep(s);
-    }
+    for (int s = 0; s < L.in4 / 4; ++s) kstep(s);
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -170,5 +163,92 @@ __device__ __forceinline__ nf4 mlp_tile(const MlpDev& net, const MlpLds& L, cons
   for (int r = 0; r < 4; ++r) y[r] = mlp_out(y[r], net.out_act, net.out_scale);
   return y;
 }
+
+// ------------------------------------------------------------------ weights in registers
+// The A operands of a network of DEPTH hidden layers and eight padded inputs,
+// as one wave holds them for whole 16-sample tiles: lane l keeps, per step of
+// four of the K dimension, the weight of neuron l % 16 of each tile for the
+// input row of its lane group.  A network of two layers of 64 takes 88
+// registers and 36 of biases, so that three waves share a SIMD and each
+// evaluates tile after tile without reading a weight again; the LDS image
+// above costs a workgroup more time to stage than its four tiles take.
+constexpr int kRegIn4 = 8;
+template <int W, int DEPTH>
+struct MlpRegs {
+  static constexpr int NT = W / 16, KS = W / 4;
+  float w0[kRegIn4 / 4][NT], wh[DEPTH > 1 ? DEPTH - 1 : 1][KS][NT], wo[KS];
+  nf4 b0[NT], bh[DEPTH > 1 ? DEPTH - 1 : 1][NT], bo;
+
+  __device__ __forceinline__ void load(const MlpDev& net, int lane) {
+    const int g = lane >> 4, c = lane & 15, in = net.in_dim, out = net.out_dim;
+    const float* p = net.p;
+#pragma unroll
+    for (int s = 0; s < kRegIn4 / 4; ++s)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w0[s][t] = 4 * s + g < in ? p[(4 * s + g) * W + 16 * t + c] : 0.0f;
+    p += in * W;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) b0[t][r] = p[16 * t + 4 * g + r];
+    p += W;
+#pragma unroll
+    for (int l = 0; l + 1 < DEPTH; ++l) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) wh[l][s][t] = p[(16 * (s >> 2) + 4 * g + (s & 3)) * W + 16 * t + c];
+      p += W * W;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) bh[l][t][r] = p[16 * t + 4 * g + r];
+      p += W;
+    }
+#pragma unroll
+    for (int s = 0; s < KS; ++s) wo[s] = c < out ? p[(16 * (s >> 2) + 4 * g + (s & 3)) * out + c] : 0.0f;
+    p += W * out;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bo[r] = 4 * g + r < out ? p[4 * g + r] : 0.0f;
+  }
+
+  // the network for the wave's 16 samples, f[s] = input feature 4 s + l / 16
+  // of the lane's sample; outputs as mlp_tile returns them (the same products
+  // in the same order)
+  template <int ACT>
+  __device__ __forceinline__ nf4 eval(const float (&f)[kRegIn4 / 4], int out_act, float scale) const {
+    nf4 h[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) h[t] = b0[t];
+#pragma unroll
+    for (int s = 0; s < kRegIn4 / 4; ++s)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) h[t] = mfma_f32_16x16x4(w0[s][t], f[s], h[t]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h[t][r] = mlp_act<ACT>(h[t][r]);
+#pragma unroll
+    for (int l = 0; l + 1 < DEPTH; ++l) {
+      nf4 o[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) o[t] = bh[l][t];
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o[t] = mfma_f32_16x16x4(wh[l][s][t], h[s >> 2][s & 3], o[t]);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[t][r] = mlp_act<ACT>(o[t][r]);
+    }
+    nf4 y = bo;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) y = mfma_f32_16x16x4(wo[s], h[s >> 2][s & 3], y);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = mlp_out(y[r], out_act, scale);
+    return y;
+  }
+};
 
 }  // namespace cbic
