@@ -32,7 +32,8 @@ hipError_t allow_lds(K kernel, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                              int(bytes));
 }
-constexpr int kSelectWG = 1024;
+
+__device__ __forceinline__ void sel_clear(uint32_t* __restrict__ sc, int N);
 
 // score[b] = net(x_b, tau_b), tau_b = (T_max - T_b) / T_max (FP64 inputs
 // rounded to FP32, as the network computes in FP32); without T the network
@@ -40,7 +41,10 @@ constexpr int kSelectWG = 1024;
 template <int W, int ACT>
 __global__ void __launch_bounds__(kNetWG) mlp_score(MlpDev net, MlpLds L, int B, int n,
                                                     const double* __restrict__ x, const int32_t* __restrict__ T,
-                                                    int Tmax, float* __restrict__ score) {
+                                                    int Tmax, float* __restrict__ score, uint32_t* __restrict__ sc,
+                                                    int N) {
+  // the selection's scratch, for the launches after this one
+  if (sc && blockIdx.x == 0) sel_clear(sc, N);
   extern __shared__ float lds[];
   mlp_stage(net, L, lds);
   const int lane = threadIdx.x & 63;
@@ -85,7 +89,9 @@ __global__ void __launch_bounds__(kNetWG) mlp_rows(MlpDev net, MlpLds L, int B, 
 template <int W, int ACT, int DEPTH>
 __global__ void __launch_bounds__(kNetWG, 3) mlp_score_r(MlpDev net, int B, int n, const double* __restrict__ x,
                                                          const int32_t* __restrict__ T, int Tmax,
-                                                         float* __restrict__ score) {
+                                                         float* __restrict__ score, uint32_t* __restrict__ sc, int N) {
+  // the selection's scratch, for the launches after this one
+  if (sc && blockIdx.x == 0) sel_clear(sc, N);
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int nwaves = gridDim.x * (kNetWG / 64);
   MlpRegs<W, DEPTH> w;
@@ -176,28 +182,96 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wtot, uint3
 // The N highest scores of Bc, in ascending index order (equal scores: lower
 // index first): a radix select of the N-th largest key (11 + 11 + 10 bits)
 // and an order-preserving compaction that also gathers the selected rows of
-// x (n wide) and T.  The work is spread over blocks of kSelChunk keys; a
-// one-block kernel between the histogram passes finds the digit.  Scratch
-// (uint32): hist [2048], state {prefix, mask, left} at kSelState, then per
-// block: greater count, equal count, output base, tie base.
-constexpr int kSelWG = 256, kSelE = 16, kSelChunk = kSelWG * kSelE;
+// x (n wide) and T.  Up to kSelSmall keys one workgroup does it all with the
+// keys in registers (sel_small).  Larger sets are spread over blocks of
+// kSelChunk keys, and the block that finishes a pass last does the pass's
+// one-block part, so that a pass is one launch; the scoring kernel before them
+// clears the scratch.  Scratch (uint32): hist [2048], state {prefix, mask, left,
+// blocks done} at kSelState, then per block: greater count, equal count,
+// output base, tie base.  Launch- and latency-bound: 163840 keys take five
+// launches and 41 us, 3000 keys one launch and 13 us; with a launch of its own
+// for every part it was ten launches, 59 and 45 us.
+constexpr int kSelWG = 256, kSelE = 8, kSelChunk = kSelWG * kSelE;
 constexpr int kSelState = 2048, kSelBlocks = 2056;
+constexpr int kSmallWG = 1024, kSmallE = 16, kSelSmall = kSmallWG * kSmallE;
 
-__global__ void __launch_bounds__(kSelectWG) sel_init(uint32_t* __restrict__ sc, int N) {
-  for (int i = threadIdx.x; i < 2048; i += kSelectWG) sc[i] = 0u;
-  if (threadIdx.x == 0) {
-    sc[kSelState] = 0u;
-    sc[kSelState + 1] = 0u;
-    sc[kSelState + 2] = uint32_t(N);
-  }
+// cleared scratch for a selection of N, by one block of any size
+__device__ __forceinline__ void sel_clear(uint32_t* __restrict__ sc, int N) {
+  for (int i = threadIdx.x; i < kSelBlocks; i += blockDim.x) sc[i] = i == kSelState + 2 ? uint32_t(N) : 0u;
 }
 
+// The digit of the left-th largest key from the histogram h[0..nb) of the
+// remaining keys' digits (WG threads; nb a multiple of WG): *bin, and in *rest
+// the keys still to take within that bin.  The keys in the bins above a
+// thread's own come from a suffix sum over the threads.
+template <int WG>
+__device__ __forceinline__ void sel_digit(const uint32_t* h, uint32_t nb, uint32_t left, uint32_t* wtot,
+                                          uint32_t* bin, uint32_t* rest) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int per = int(nb) / WG;
+  uint32_t mine = 0;
+  for (int j = 0; j < per; ++j) mine += h[per * t + j];
+  uint32_t inc = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_down(inc, o, 64);
+    if (lane + o < 64) inc += u;
+  }
+  if (lane == 0) wtot[wave] = inc;
+  if (t == 0) {
+    *bin = 0u;
+    *rest = left;
+  }
+  __syncthreads();
+  uint32_t above = inc - mine;
+#pragma unroll
+  for (int w = 0; w < WG / 64; ++w) above += w > wave ? wtot[w] : 0u;
+  for (int j = per - 1; j >= 0; --j) {
+    const uint32_t c = h[per * t + j];
+    if (above < left && left <= above + c) {
+      *bin = uint32_t(per * t + j);
+      *rest = left - above;
+    }
+    above += c;
+  }
+  __syncthreads();
+}
+
+// What the blocks of a pass tell the last one passes through device-scope
+// atomics alone: an update returns a value that the thread waits for (so it
+// has taken place, at the one point all dies of the chip share, before the
+// block counts itself done), and the last block reads with atomic loads.  A
+// fence instead would write back and invalidate the die's whole L2 for every
+// block (a pass over 163840 keys 14 us; with the returned values 9 us).
+__device__ __forceinline__ uint32_t sel_add(uint32_t* p, uint32_t v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t sel_put(uint32_t* p, uint32_t v) {
+  return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t sel_read(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// whether this block is the last of the grid's G to come here; `seen` gathers
+// the values its updates returned
+__device__ __forceinline__ bool sel_last(uint32_t* sc, int G, uint32_t* flag, uint32_t seen) {
+  asm volatile("" ::"v"(seen) : "memory");  // the returned values have arrived
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *flag = __hip_atomic_fetch_add(&sc[kSelState + 3], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == uint32_t(G) - 1u;
+  __syncthreads();
+  return *flag != 0u;
+}
+
+// One pass: the digits of the keys that match the prefix so far; the last
+// block finds the next digit and clears the histogram for the next pass.
 __global__ void __launch_bounds__(kSelWG) sel_hist(const float* __restrict__ score, int Bc, uint32_t* __restrict__ sc,
                                                    int shift, uint32_t nb) {
   __shared__ uint32_t h[2048];
+  __shared__ uint32_t wtot[kSelWG / 64], s_bin, s_left, s_flag;
   const int t = threadIdx.x;
   for (uint32_t i = t; i < nb; i += kSelWG) h[i] = 0u;
-  const uint32_t prefix = sc[kSelState], mask = sc[kSelState + 1];
+  const uint32_t prefix = sc[kSelState], mask = sc[kSelState + 1], left = sc[kSelState + 2];
   __syncthreads();
   const int base = blockIdx.x * kSelChunk;
   uint32_t k[kSelE];
@@ -210,60 +284,36 @@ __global__ void __launch_bounds__(kSelWG) sel_hist(const float* __restrict__ sco
   for (int j = 0; j < kSelE; ++j)
     if (base + j * kSelWG + t < Bc && (k[j] & mask) == prefix) atomicAdd(&h[(k[j] >> shift) & (nb - 1u)], 1u);
   __syncthreads();
-  for (uint32_t i = t; i < nb; i += kSelWG)
-    if (h[i]) atomicAdd(&sc[i], h[i]);
-}
-
-// One block: the digit of the left-th largest remaining key.  Thread t owns
-// bins 2t + 1 and 2t (bin t in the 1024-bin pass); the keys in the bins above
-// them come from a suffix sum over the threads.  Clears the histogram.
-__global__ void __launch_bounds__(kSelectWG) sel_find(uint32_t* __restrict__ sc, int shift, uint32_t nb) {
-  __shared__ uint32_t wtot[kSelectWG / 64];
-  __shared__ uint32_t s_bin, s_left;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const uint32_t left = sc[kSelState + 2];
-  const int per = int(nb) / kSelectWG;
-  const int hi = per == 2 ? 2 * t + 1 : t;
-  const uint32_t hh = sc[hi], hl = per == 2 ? sc[hi - 1] : 0u;
-  const uint32_t mine = hh + hl;
-  uint32_t inc = mine;
+  uint32_t got[2048 / kSelWG] = {}, seen = 0;  // (all issued before the first is waited for)
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t u = __shfl_down(inc, o, 64);
-    if (lane + o < 64) inc += u;
+  for (int j = 0; j < 2048 / kSelWG; ++j) {
+    const uint32_t i = j * kSelWG + t;
+    if (i < nb && h[i]) got[j] = sel_add(&sc[i], h[i]);
   }
-  if (lane == 0) wtot[wave] = inc;
-  if (t == 0) {
-    s_bin = 0u;
-    s_left = left;
-  }
-  __syncthreads();
-  uint32_t above = inc - mine;
 #pragma unroll
-  for (int w = 0; w < kSelectWG / 64; ++w) above += w > wave ? wtot[w] : 0u;
-  __syncthreads();
-  if (above < left && left <= above + hh) {
-    s_bin = uint32_t(hi);
-    s_left = left - above;
-  } else if (per == 2 && above + hh < left && left <= above + hh + hl) {
-    s_bin = uint32_t(hi - 1);
-    s_left = left - above - hh;
+  for (int j = 0; j < 2048 / kSelWG; ++j) seen |= got[j];
+  if (!sel_last(sc, int(gridDim.x), &s_flag, seen)) return;
+  for (uint32_t i = t; i < nb; i += kSelWG) {
+    h[i] = sel_read(&sc[i]);
+    sc[i] = 0u;
   }
   __syncthreads();
-  for (uint32_t i = t; i < nb; i += kSelectWG) sc[i] = 0u;
+  sel_digit<kSelWG>(h, nb, left, wtot, &s_bin, &s_left);
   if (t == 0) {
-    sc[kSelState] |= s_bin << shift;
-    sc[kSelState + 1] |= (nb - 1u) << shift;
+    sc[kSelState] = prefix | (s_bin << shift);
+    sc[kSelState + 1] = mask | ((nb - 1u) << shift);
     sc[kSelState + 2] = s_left;
+    sc[kSelState + 3] = 0u;
   }
 }
 
-// Per block: keys above the threshold key and keys equal to it.
+// Per block: keys above the threshold key and keys equal to it; the last
+// block forms each block's first output position and first tie rank.
 __global__ void __launch_bounds__(kSelWG) sel_count(const float* __restrict__ score, int Bc,
-                                                    uint32_t* __restrict__ sc, int G) {
-  __shared__ uint32_t wtot[kSelWG / 64];
-  const int t = threadIdx.x;
-  const uint32_t thr = sc[kSelState];
+                                                    uint32_t* __restrict__ sc) {
+  __shared__ uint32_t wtot[kSelWG / 64], s_flag;
+  const int t = threadIdx.x, G = int(gridDim.x);
+  const uint32_t thr = sc[kSelState], left = sc[kSelState + 2];
   const int base = blockIdx.x * kSelChunk;
   uint32_t gt = 0, eq = 0;
 #pragma unroll
@@ -273,27 +323,22 @@ __global__ void __launch_bounds__(kSelWG) sel_count(const float* __restrict__ sc
     gt += (i < Bc && k > thr) ? 1u : 0u;
     eq += (i < Bc && k == thr) ? 1u : 0u;
   }
-  uint32_t tg, te;
+  uint32_t tg, te, tt;
   block_scan<kSelWG>(gt, wtot, tg);
   block_scan<kSelWG>(eq, wtot, te);
+  uint32_t seen = 0;
   if (t == 0) {
-    sc[kSelBlocks + blockIdx.x] = tg;
-    sc[kSelBlocks + G + blockIdx.x] = te;
+    const uint32_t a = sel_put(&sc[kSelBlocks + blockIdx.x], tg), b = sel_put(&sc[kSelBlocks + G + blockIdx.x], te);
+    seen = a | b;
   }
-}
-
-// One block: each block's first output position and first tie rank.
-__global__ void __launch_bounds__(kSelectWG) sel_offsets(uint32_t* __restrict__ sc, int G) {
-  __shared__ uint32_t wtot[kSelectWG / 64];
-  const uint32_t left = sc[kSelState + 2];
+  if (!sel_last(sc, G, &s_flag, seen)) return;
   uint32_t out_run = 0, tie_run = 0;
-  for (int c = 0; c < G; c += kSelectWG) {
-    const int b = c + threadIdx.x;
-    const uint32_t gt = b < G ? sc[kSelBlocks + b] : 0u, eq = b < G ? sc[kSelBlocks + G + b] : 0u;
-    uint32_t te, tt;
-    const uint32_t tie0 = tie_run + block_scan<kSelectWG>(eq, wtot, te);
-    const uint32_t ties_taken = tie0 >= left ? 0u : min(eq, left - tie0);
-    const uint32_t out0 = out_run + block_scan<kSelectWG>(gt + ties_taken, wtot, tt);
+  for (int c = 0; c < G; c += kSelWG) {
+    const int b = c + t;
+    const uint32_t bg = b < G ? sel_read(&sc[kSelBlocks + b]) : 0u, be = b < G ? sel_read(&sc[kSelBlocks + G + b]) : 0u;
+    const uint32_t tie0 = tie_run + block_scan<kSelWG>(be, wtot, te);
+    const uint32_t ties_taken = tie0 >= left ? 0u : min(be, left - tie0);
+    const uint32_t out0 = out_run + block_scan<kSelWG>(bg + ties_taken, wtot, tt);
     if (b < G) {
       sc[kSelBlocks + 2 * G + b] = out0;
       sc[kSelBlocks + 3 * G + b] = tie0;
@@ -301,6 +346,47 @@ __global__ void __launch_bounds__(kSelectWG) sel_offsets(uint32_t* __restrict__ 
     out_run += tt;
     tie_run += te;
   }
+}
+
+// The rows of the selected indices sel[p0..p1) (written by this block before
+// a barrier), by the block's threads, element by element.
+__device__ __forceinline__ void sel_gather(const int32_t* sel, int p0, int p1, int n, const double* __restrict__ x,
+                                           const int32_t* __restrict__ T, double* __restrict__ xs,
+                                           int32_t* __restrict__ Ts) {
+  if (xs)
+    for (long e = long(p0) * n + threadIdx.x; e < long(p1) * n; e += blockDim.x) {
+      const int p = int(e / n), q = int(e - long(p) * n);
+      xs[e] = x[size_t(sel[p]) * n + q];
+    }
+  if (Ts)
+    for (int p = p0 + threadIdx.x; p < p1; p += blockDim.x) Ts[p] = T[sel[p]];
+}
+
+// The selected among a thread's E consecutive keys from i0: bit j of `gt`
+// for a key above the threshold, of `eq` for one equal to it.
+template <int E>
+__device__ __forceinline__ void sel_flags(const uint32_t (&k)[E], int i0, int Bc, uint32_t thr, uint32_t& gt,
+                                          uint32_t& eq) {
+  gt = 0;
+  eq = 0;
+#pragma unroll
+  for (int j = 0; j < E; ++j) {
+    if (i0 + j < Bc && k[j] > thr) gt |= 1u << j;
+    if (i0 + j < Bc && k[j] == thr) eq |= 1u << j;
+  }
+}
+// of those flags the ones taken: all above, and the ties whose rank (from
+// `rank` on) is below `left`
+template <int E>
+__device__ __forceinline__ uint32_t sel_take(uint32_t gt, uint32_t eq, uint32_t rank, uint32_t left) {
+  uint32_t take = gt;
+#pragma unroll
+  for (int j = 0; j < E; ++j)
+    if ((eq >> j) & 1u) {
+      if (rank < left) take |= 1u << j;
+      ++rank;
+    }
+  return take;
 }
 
 // Per block: write the selected indices (and rows) in ascending index order;
@@ -314,39 +400,64 @@ __global__ void __launch_bounds__(kSelWG) sel_scatter(const float* __restrict__ 
   const int t = threadIdx.x;
   const uint32_t thr = sc[kSelState], left = sc[kSelState + 2];
   const int i0 = blockIdx.x * kSelChunk + kSelE * t;
-  uint32_t gt = 0, eq = 0, neq = 0;
+  uint32_t k[kSelE], gt, eq, te, tt;
 #pragma unroll
-  for (int j = 0; j < kSelE; ++j) {
-    const int i = i0 + j;
-    const uint32_t k = i < Bc ? score_key(score[i]) : 0u;
-    if (i < Bc && k > thr) gt |= 1u << j;
-    if (i < Bc && k == thr) {
-      eq |= 1u << j;
-      ++neq;
-    }
-  }
-  uint32_t te, tt;
-  uint32_t rank = sc[kSelBlocks + 3 * G + blockIdx.x] + block_scan<kSelWG>(neq, wtot, te);
-  uint32_t take = gt;
-#pragma unroll
-  for (int j = 0; j < kSelE; ++j)
-    if ((eq >> j) & 1u) {
-      if (rank < left) take |= 1u << j;
-      ++rank;
-    }
-  uint32_t pos = sc[kSelBlocks + 2 * G + blockIdx.x] + block_scan<kSelWG>(__popc(take), wtot, tt);
+  for (int j = 0; j < kSelE; ++j) k[j] = i0 + j < Bc ? score_key(score[i0 + j]) : 0u;
+  sel_flags<kSelE>(k, i0, Bc, thr, gt, eq);
+  const uint32_t rank = sc[kSelBlocks + 3 * G + blockIdx.x] + block_scan<kSelWG>(__popc(eq), wtot, te);
+  const uint32_t take = sel_take<kSelE>(gt, eq, rank, left);
+  const uint32_t first = sc[kSelBlocks + 2 * G + blockIdx.x];
+  uint32_t pos = first + block_scan<kSelWG>(__popc(take), wtot, tt);
 #pragma unroll
   for (int j = 0; j < kSelE; ++j)
     if ((take >> j) & 1u) {
-      const int i = i0 + j;
-      if (pos < uint32_t(N)) {
-        sel[pos] = i;
-        if (xs)
-          for (int q = 0; q < n; ++q) xs[size_t(pos) * n + q] = x[size_t(i) * n + q];
-        if (Ts) Ts[pos] = T[i];
-      }
+      if (pos < uint32_t(N)) sel[pos] = i0 + j;
       ++pos;
     }
+  __syncthreads();
+  sel_gather(sel, int(first), min(int(first + tt), N), n, x, T, xs, Ts);
+}
+
+// The whole selection in one workgroup for Bc <= kSelSmall.
+__global__ void __launch_bounds__(kSmallWG) sel_small(const float* __restrict__ score, int Bc, int N,
+                                                      int32_t* __restrict__ sel, int n, const double* __restrict__ x,
+                                                      const int32_t* __restrict__ T, double* __restrict__ xs,
+                                                      int32_t* __restrict__ Ts) {
+  __shared__ uint32_t h[2048];
+  __shared__ uint32_t wtot[kSmallWG / 64], s_bin, s_left;
+  const int t = threadIdx.x, i0 = kSmallE * t;
+  uint32_t k[kSmallE];
+#pragma unroll
+  for (int j = 0; j < kSmallE; ++j) k[j] = i0 + j < Bc ? score_key(score[i0 + j]) : 0u;
+  uint32_t prefix = 0, mask = 0, left = uint32_t(N);
+#pragma unroll
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+    const uint32_t nb = pass < 2 ? 2048u : 1024u;
+    for (uint32_t i = t; i < nb; i += kSmallWG) h[i] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallE; ++j)
+      if (i0 + j < Bc && (k[j] & mask) == prefix) atomicAdd(&h[(k[j] >> shift) & (nb - 1u)], 1u);
+    __syncthreads();
+    sel_digit<kSmallWG>(h, nb, left, wtot, &s_bin, &s_left);
+    prefix |= s_bin << shift;
+    mask |= (nb - 1u) << shift;
+    left = s_left;
+    __syncthreads();
+  }
+  uint32_t gt, eq, te, tt;
+  sel_flags<kSmallE>(k, i0, Bc, prefix, gt, eq);
+  const uint32_t take = sel_take<kSmallE>(gt, eq, block_scan<kSmallWG>(__popc(eq), wtot, te), left);
+  uint32_t pos = block_scan<kSmallWG>(__popc(take), wtot, tt);
+#pragma unroll
+  for (int j = 0; j < kSmallE; ++j)
+    if ((take >> j) & 1u) {
+      if (pos < uint32_t(N)) sel[pos] = i0 + j;
+      ++pos;
+    }
+  __syncthreads();
+  sel_gather(sel, 0, N, n, x, T, xs, Ts);
 }
 
 // ------------------------------------------------------------------ actor rollout
@@ -628,15 +739,26 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   const dim3 grid((Bc + kNetWG / 4 - 1) / (kNetWG / 4)), rgrid(reg_blocks(Bc, ctx->device)), block(kNetWG);
   const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
+  // scratch of the selection beyond one workgroup's
+  const int G = (Bc + kSelChunk - 1) / kSelChunk;
+  uint32_t* sc = nullptr;
+  std::unique_lock<std::mutex> lk(ctx->mu, std::defer_lock);
+  if (N > 0 && Bc > kSelSmall) {
+    lk.lock();
+    void* aux = nullptr;
+    if (cbic_status e = context_aux(ctx, (size_t(kSelBlocks) + 4 * size_t(G)) * sizeof(uint32_t), &aux)) return e;
+    sc = static_cast<uint32_t*>(aux);
+    if (ctx->have_last && ctx->last_stream != st) HIP_TRY(hipStreamWaitEvent(st, ctx->done_ev, 0));
+  }
 #define CBIC_SCORE(WW, AA)                                                                                      \
   do {                                                                                                          \
     if (regs && d.depth == 1)                                                                                   \
-      hipLaunchKernelGGL((mlp_score_r<WW, AA, 1>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score);    \
+      hipLaunchKernelGGL((mlp_score_r<WW, AA, 1>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score, sc, N); \
     else if (regs)                                                                                              \
-      hipLaunchKernelGGL((mlp_score_r<WW, AA, 2>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score);    \
+      hipLaunchKernelGGL((mlp_score_r<WW, AA, 2>), rgrid, block, 0, st, d, Bc, n, d_x, d_T, T_max, d_score, sc, N); \
     else {                                                                                                      \
       HIP_TRY(allow_lds(mlp_score<WW, AA>, lds));                                                               \
-      hipLaunchKernelGGL((mlp_score<WW, AA>), grid, block, lds, st, d, L, Bc, n, d_x, d_T, T_max, d_score);     \
+      hipLaunchKernelGGL((mlp_score<WW, AA>), grid, block, lds, st, d, L, Bc, n, d_x, d_T, T_max, d_score, sc, N); \
     }                                                                                                           \
   } while (0)
   if (net->width == 32) {
@@ -650,22 +772,14 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   }
 #undef CBIC_SCORE
   HIP_TRY(hipGetLastError());
-  if (N > 0) {
-    const int G = (Bc + kSelChunk - 1) / kSelChunk;
-    std::lock_guard<std::mutex> lk(ctx->mu);
-    void* aux = nullptr;
-    if (cbic_status e = context_aux(ctx, (size_t(kSelBlocks) + 4 * size_t(G)) * sizeof(uint32_t), &aux)) return e;
-    uint32_t* sc = static_cast<uint32_t*>(aux);
-    if (ctx->have_last && ctx->last_stream != st) HIP_TRY(hipStreamWaitEvent(st, ctx->done_ev, 0));
-    hipLaunchKernelGGL(sel_init, dim3(1), dim3(kSelectWG), 0, st, sc, N);
-    for (int pass = 0; pass < 3; ++pass) {
-      const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
-      const uint32_t nb = pass < 2 ? 2048u : 1024u;
-      hipLaunchKernelGGL(sel_hist, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc, shift, nb);
-      hipLaunchKernelGGL(sel_find, dim3(1), dim3(kSelectWG), 0, st, sc, shift, nb);
-    }
-    hipLaunchKernelGGL(sel_count, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc, G);
-    hipLaunchKernelGGL(sel_offsets, dim3(1), dim3(kSelectWG), 0, st, sc, G);
+  if (N > 0 && !sc) {
+    hipLaunchKernelGGL(sel_small, dim3(1), dim3(kSmallWG), 0, st, d_score, Bc, N, d_sel, n, d_x, d_T, d_x_sel, d_T_sel);
+    HIP_TRY(hipGetLastError());
+  } else if (sc) {
+    for (int pass = 0; pass < 3; ++pass)
+      hipLaunchKernelGGL(sel_hist, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc, pass == 0 ? 21 : (pass == 1 ? 10 : 0),
+                         pass < 2 ? 2048u : 1024u);
+    hipLaunchKernelGGL(sel_count, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc);
     hipLaunchKernelGGL(sel_scatter, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, N, d_sel, n, d_x, d_T, d_x_sel,
                        d_T_sel, sc, G);
     HIP_TRY(hipGetLastError());

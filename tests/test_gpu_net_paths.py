@@ -71,3 +71,24 @@ def test_actor_controls_are_the_networks(ctx, kind, width, depth):
         live = (k < T[:, None])[..., None]
         np.testing.assert_array_equal(U, np.where(live, y, 0).astype(np.float64))
     sysm.close()
+
+
+@pytest.mark.parametrize("Bc,N", [(1, 1), (1023, 1022), (16384, 1), (16384, 16384), (16385, 5000), (18432, 18432),
+                                  (18433, 2049), (600001, 3)])
+@pytest.mark.parametrize("levels", [0, 3], ids=["distinct", "ties"])
+def test_selection_at_path_edges(ctx, Bc, N, levels):
+    # one workgroup up to 16384 keys, blocks of 2048 beyond; `levels` states
+    # only: long runs of equal scores
+    import torch
+    from paper_2602_19699_amd import cbic
+    g, _ = _net(5, 32, 1, 1, seed=9)
+    x, T, Tm = I.bic_candidates("pm16k", Bc, seed=Bc)
+    if levels:
+        x, T = np.tile(x[:levels], (Bc // levels + 1, 1))[:Bc], np.full(Bc, 7, np.int32)
+    s, sel, xs, Ts = cbic.bic_select(ctx, g, torch.as_tensor(x, device="cuda"), torch.as_tensor(T, device="cuda"), Tm, N,
+                                     gather=True)
+    s, sel, xs, Ts = (v.cpu().numpy() for v in (s, sel, xs, Ts))
+    want = np.sort(np.lexsort((np.arange(Bc), -s))[:N])
+    np.testing.assert_array_equal(sel, want)
+    np.testing.assert_array_equal(xs, x[want])
+    np.testing.assert_array_equal(Ts, T[want])
