@@ -2,32 +2,44 @@
 // (q in R^19, v in R^18, u in R^12; paper Sec. II eq. 1 and Sec. IV).
 //
 // One 256-thread workgroup owns one instance.  The backward Riccati sweep
-// keeps P, f_x, P f_x, f_u, P f_u, the gains and Q_ux in LDS and forms the
+// keeps P, [f_x | f_u], P [f_x | f_u], the gains and Q_ux in LDS and forms the
 // products as 16 x 16 output tiles on the matrix cores (FP32 MFMA for the
 // mixed form, FP64 MFMA for the plain one), the tiles spread over the four
-// waves; Q_uu is factored in FP64 (wave 0, rows held by lanes, each pivot
-// column broadcast from its lane through a scalar register) in both
-// precisions.  The dynamics step needs a Cholesky of the 18 x 18 mass matrix
-// M(q) = A^T A + diag(1 + 0.1 sin q); a wave does it with its lanes holding
-// the rows.  The dynamics Jacobians do not depend on P, so the sweep
-// evaluates them ahead of the recursion, CH steps at a time with every wave
-// taking its own steps, into per-slot blocks in HBM that the recursion then
-// reads back.  Line-search trials run one per wave: in
-// round r wave w tries alpha_j with j = 4 r + w, and the first accepted j is
-// taken, as in the sequential rule.  Trajectories and gains use the same
-// step-major workspace as the lane schedule.
+// waves (see backward); Q_uu is factored in FP64 (one wave, rows held by
+// lanes) in both precisions.  The dynamics step needs a Cholesky of the 18 x
+// 18 mass matrix M(q) = A^T A + diag(1 + 0.1 sin q); a wave does it with its
+// lanes holding the rows.  The dynamics Jacobians do not depend on P, so the
+// sweep evaluates them ahead of the recursion, CH steps at a time with every
+// wave taking its own steps, into per-slot blocks in HBM that the recursion
+// then reads back.  Line-search trials run one per wave: in round r wave w
+// tries alpha_j with j = 4 r + w, and the first accepted j is taken, as in the
+// sequential rule.  Trajectories and gains use the same step-major workspace
+// as the lane schedule.
 #include "lane_launch.hpp"
 
 namespace cbic {
 namespace quad {
 
 constexpr int NQ = 19, NV = 18, N = 37, M = 12;
-constexpr int LD = 40;   // row stride of 37-wide LDS matrices
-constexpr int LDB = 13;  // row stride of 12-wide LDS matrices
+constexpr int LD = 40;   // length of a state vector in LDS
 constexpr int NT = 256;  // threads per workgroup
 constexpr int NW = NT / 64;
-constexpr int DB = N * (N + M);  // derivative block [f_x | f_u], row-major 37 x 49
-constexpr int CH = 16;           // steps per chunk of precomputed derivative blocks
+// A matrix operand of a product with inner size 37 is kept row by row with the
+// inner index k at kpos(k), the indices that one lane group of the matrix
+// instruction takes (k = lk, lk + 4, ...) side by side, so that a lane reads
+// its ten values of a row in three (FP64: five) wide loads; places past 36
+// that are read hold zeros.  kq: the same for inner size 12.
+constexpr int KG = 12, KROW = 4 * KG;  // places per lane group and row
+__host__ __device__ constexpr int kpos(int k) { return (k & 3) * KG + (k >> 2); }
+__host__ __device__ constexpr int kq(int t) { return (t & 3) * 4 + (t >> 2); }
+// row strides in LDS: sixteen rows read by 16-byte pieces start on sixteen
+// different groups of banks
+template <class R> struct Stride { static constexpr int k = 52; };
+template <> struct Stride<double> { static constexpr int k = 50; };
+constexpr int SQ = 20;
+constexpr int BROW = 48;                // first LDS row of f_u^T behind f_x^T's three 16-row blocks
+constexpr int DB = (N + M) * KROW;      // derivative block: the 49 columns of [f_x | f_u] as operand rows
+constexpr int CH = 12;                  // steps per chunk of precomputed derivative blocks
 
 // device block: [dt, w_u, w_T, w_q, w_v, M0 = A^T A (18x18), W1, W2, e(18), x_nom(37)]
 constexpr int O_DT = 0, O_WU = 1, O_WT = 2, O_WQ = 3, O_WV = 4, O_M0 = 5, O_W1 = O_M0 + 324,
@@ -54,23 +66,22 @@ struct Smem {
   R W2[NV][NV + 1];
   R e[NV];
   R xnom[LD];
-  R P[N][LD];   // value Hessian; Q_xx; the updated P
-  R A[N][LD];   // f_x
-  R PA[N][LD];  // P f_x; right-hand sides of the Jacobian solves; scratch
-  R Bm[N][LDB]; // f_u
-  // P f_u; once Q_uu is formed, the bounded step's copy of Q_uu and the
-  // reciprocal pivots of its face factors live here (box_step)
-  alignas(8) R PB[N][LDB];
-  R Kg[M][LD];  // feedback gain (m x n)
-  R Qux[M][LD];
-  R p[LD], Qx[LD];
+  alignas(16) R P[48][Stride<R>::k];       // value Hessian (operand rows; symmetric), row 37: its gradient p
+  alignas(16) R AT[2][64][Stride<R>::k];   // [f_x | f_u]^T of this and the next step: rows 0..36 and BROW..BROW+11
+  alignas(16) R PAT[64][Stride<R>::k];     // (P [f_x | f_u])^T, the same rows; scratch of the update
+  alignas(16) R QuxT[48][SQ], KT[48][SQ];  // Q_ux^T and the feedback gain's transpose (places kq)
+  alignas(16) R Lr[M][16];                 // factor of Q_uu in R
+  R Lri[M];                                // reciprocals of its diagonal
+  R Qg[N + M];                             // f_x^T p, f_u^T p
+  R xs[2][LD], us[2][16];                  // state and control of this and the next step
   R Qu[16], kk[16];
   double Quu[M][M + 1];
-  double Lq[M][M + 1];
-  double Lqi[M];  // reciprocals of the diagonal of Lq
+  // the bounded step's face factor
+  double Lq[M][M + 1], Lqi[M], Li[M];
   double wJ[NW];
   int wok[NW];
-  int flag;
+  int flag;     // Q_uu did not factor (then the bounded step's state)
+  int nonfin;   // the gains are not finite
   unsigned Hq_held;  // components held at a bound by the bounded step
   WaveScratch<R> wv[NW];
 };
@@ -94,6 +105,17 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// v, opaque to the compiler: what is derived from it (addresses, lane masks) is
+// formed where it is used.  Derived from the lane number itself, they are
+// invariant over the whole solve, and the compiler keeps hundreds of them
+// through it, in scratch memory (145 registers of the mixed kernel for two
+// instances per CU, 173 of the FP64 one; with them 11.2 instead of 8.8 ms, and
+// 11.1 instead of 9.3).
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
 }
 
 // value of v in lane j (j uniform), read through a scalar register
@@ -145,7 +167,8 @@ __device__ __forceinline__ void stage_constants(S& sm, const double* __restrict_
 // One semi-implicit Euler step for wave scratch ws: reads ws.x and ws.u,
 // writes ws.xn; leaves L (factor of M), a, sin/cos and W2 cos q in ws.
 template <class R, class S>
-__device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, int lane) {
+__device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, int lane_) {
+  const int lane = fresh(lane_);
   if (lane < NV) {
     R sn, cs;
     dsincos_lib(ws.x[lane], &sn, &cs);
@@ -239,13 +262,13 @@ __device__ __forceinline__ R wave_cost(const S& sm, const R* x, const R* u, cons
 }
 
 // ------------------------------------------------------------------ MFMA tiles
-// One 16 x 16 output tile of C = Cin + op(A) op(B) (inner size Kd) by one wave
-// with 16x16x4 matrix-core instructions: FP32 for the mixed form, FP64 for the
-// plain one.  Lane l supplies A(i0 + l % 16, k0 + l / 16) and
-// B(k0 + l / 16, j0 + l % 16) per step of 4; its result register r holds
-// C(i0 + 4 (l / 16) + r, j0 + l % 16) in FP32 and C(i0 + l / 16 + 4 r,
-// j0 + l % 16) in FP64.  Entries outside Mr x Nc x Kd enter as zeros and are
-// not stored.
+// A 16 x 16 output tile C += A B by one wave with 16x16x4 matrix-core
+// instructions: FP32 for the mixed form, FP64 for the plain one.  Lane l
+// supplies A(i0 + l % 16, k0 + l / 16) and B(k0 + l / 16, j0 + l % 16) per step
+// of 4; its result register r holds C(i0 + 4 (l / 16) + r, j0 + l % 16) in FP32
+// and C(i0 + l / 16 + 4 r, j0 + l % 16) in FP64.  With the operands swapped a
+// lane gets the transposed product's entries, the same sums of the same
+// products.
 typedef float mf_f4 __attribute__((ext_vector_type(4)));
 typedef double mf_d4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ mf_f4 mfma16(float a, float b, mf_f4 c) {
@@ -264,68 +287,56 @@ template <> struct MfAcc<double> {
   static __device__ __forceinline__ int row(int lk, int r) { return lk + 4 * r; }
 };
 
-template <int Kd, bool TA, bool TB, class R>
-__device__ __forceinline__ void mfma_tile(R* C, int ldc, const R* A, int lda, const R* Bp, int ldb, const R* Cin,
-                                          int ldcin, int Mr, int Nc, int i0, int j0, int lane) {
-  using V = typename MfAcc<R>::type;
-  const int li = lane & 15, lk = lane >> 4;
-  V acc;
+// a lane's ten values of an operand row of inner size 37 (p: the row at its
+// lane group's place)
+template <class R>
+__device__ __forceinline__ void ld_op(R (&v)[10], const R* p) {
+  if constexpr (sizeof(R) == 4) {
+    const mf_f4 a = *reinterpret_cast<const mf_f4*>(p), b = *reinterpret_cast<const mf_f4*>(p + 4);
+    const float2 c = *reinterpret_cast<const float2*>(p + 8);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + MfAcc<R>::row(lk, r), j = j0 + li;
-    acc[r] = (Cin && i < Mr && j < Nc) ? Cin[i * ldcin + j] : R(0);
-  }
-  const int ia = i0 + li, jb = j0 + li;
+    for (int i = 0; i < 4; ++i) {
+      v[i] = a[i];
+      v[4 + i] = b[i];
+    }
+    v[8] = c.x;
+    v[9] = c.y;
+  } else {
 #pragma unroll
-  for (int k0 = 0; k0 < Kd; k0 += 4) {
-    const int k = k0 + lk;
-    const R a = (ia < Mr && k < Kd) ? (TA ? A[k * lda + ia] : A[ia * lda + k]) : R(0);
-    const R b = (k < Kd && jb < Nc) ? (TB ? Bp[jb * ldb + k] : Bp[k * ldb + jb]) : R(0);
-    acc = mfma16(a, b, acc);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + MfAcc<R>::row(lk, r), j = j0 + li;
-    if (i < Mr && j < Nc) C[i * ldc + j] = acc[r];
+    for (int i = 0; i < 5; ++i) {
+      const double2 a = *reinterpret_cast<const double2*>(p + 2 * i);
+      v[2 * i] = a.x;
+      v[2 * i + 1] = a.y;
+    }
   }
 }
-
-// The same tile product handing each result to out(i, j, value) instead of
-// storing it (no input accumulator).
-template <int Kd, bool TA, bool TB, class R, class Out>
-__device__ __forceinline__ void mfma_tile_out(Out&& out, const R* A, int lda, const R* Bp, int ldb, int Mr, int Nc,
-                                              int i0, int j0, int lane) {
-  using V = typename MfAcc<R>::type;
-  const int li = lane & 15, lk = lane >> 4;
-  V acc;
+// its three values of an operand row of inner size 12
+template <class R>
+__device__ __forceinline__ void ld_op12(R (&v)[3], const R* p) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) acc[r] = R(0);
-  const int ia = i0 + li, jb = j0 + li;
-#pragma unroll
-  for (int k0 = 0; k0 < Kd; k0 += 4) {
-    const int k = k0 + lk;
-    const R a = (ia < Mr && k < Kd) ? (TA ? A[k * lda + ia] : A[ia * lda + k]) : R(0);
-    const R b = (k < Kd && jb < Nc) ? (TB ? Bp[jb * ldb + k] : Bp[k * ldb + jb]) : R(0);
-    acc = mfma16(a, b, acc);
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + MfAcc<R>::row(lk, r), j = j0 + li;
-    if (i < Mr && j < Nc) out(i, j, acc[r]);
-  }
+  for (int i = 0; i < 3; ++i) v[i] = p[i];
 }
 
 // ------------------------------------------------------------------ wave Jacobians
 // [f_x | f_u] at (ws.x, ws.u) by one wave, after wave_dyn on that point (L, its
-// reciprocal diagonal, a, sin/cos and W2 cos q in ws), written row-major
-// (37 x 49) to dst.  Lane c < 48 owns column c of the right-hand sides
-// (0..17 -dD/dq with a and v held, 18..35 -dD/dv, 36..47 the actuation S),
-// solves it with M = L L^T in registers and writes the output column that
-// depends on it: c for c < 18, c + 1 otherwise.  Lane 48 writes column 18
-// (q_18 does not enter the dynamics; only the identity).
+// reciprocal diagonal, a, sin/cos and W2 cos q in ws), written to dst column by
+// column as operand rows (kpos order, KROW places each).  Lane c < 48 owns
+// column c of the right-hand sides (0..17 -dD/dq with a and v held, 18..35
+// -dD/dv, 36..47 the actuation S), solves it with M = L L^T in registers and
+// writes the output column that depends on it: c for c < 18, c + 1 otherwise.
+// Lane 48 writes column 18 (q_18 does not enter the dynamics; only the
+// identity).
 template <class R>
-__device__ __forceinline__ void wave_jac(const Smem<R>& sm, const WaveScratch<R>& ws, R dt, int lane,
+__device__ __forceinline__ void put_op(R* __restrict__ dst, const R (&v)[N]) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int q = 0; q < 10; ++q) dst[g * KG + q] = g + 4 * q < N ? v[g + 4 * q < N ? g + 4 * q : 0] : R(0);
+}
+template <class R>
+__device__ __forceinline__ void wave_jac(const Smem<R>& sm, const WaveScratch<R>& ws, R dt, int lane_,
                                          R* __restrict__ dst) {
+  const int lane = fresh(lane_);
   if (lane < 48) {
     const int c = lane;
     R y[NV];
@@ -365,151 +376,123 @@ __device__ __forceinline__ void wave_jac(const Smem<R>& sm, const WaveScratch<R>
     // d v+_i / d (x, u)_col = [col is the velocity column i] + dt y_i; rows:
     // v+ (19..36), q+ = q + dt v+ (0..17), q_18+ = q_18 + dt e . v+
     const int col = c < NV ? c : c + 1;
-    R se = R(0);
+    R se = R(0), out[N];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const R d = ((c >= NV && c < 2 * NV && c - NV == i) ? R(1) : R(0)) + dt * y[i];
       se += sm.e[i] * d;
-      dst[(NQ + i) * (N + M) + col] = d;
-      dst[i * (N + M) + col] = ((col == i) ? R(1) : R(0)) + dt * d;
+      out[NQ + i] = d;
+      out[i] = ((col == i) ? R(1) : R(0)) + dt * d;
     }
-    dst[NV * (N + M) + col] = dt * se;
+    out[NV] = dt * se;
+    put_op(dst + col * KROW, out);
   } else if (lane == 48) {
+    R out[N];
 #pragma unroll
-    for (int r = 0; r < N; ++r) dst[r * (N + M) + NV] = (r == NV) ? R(1) : R(0);
+    for (int r = 0; r < N; ++r) out[r] = (r == NV) ? R(1) : R(0);
+    put_op(dst + NV * KROW, out);
   }
 }
 
 // ------------------------------------------------------------------ FP64 Cholesky of Q_uu and the gains
-// Wave 0 factors Quu (rows on lanes); threads 0..37 solve for [K k].  The
-// other waves run `side` meanwhile (work that needs none of the step's gains).
-template <class R, class Side>
-__device__ __forceinline__ bool gains(Smem<R>& sm, int tid, Side&& side) {
-  if (tid >= 64) side();
-  if (tid < 64) {
-    const int lane = tid;
-    const bool row = lane < M;
-    const int ri = row ? lane : 0;
-    double m[M];
-#pragma unroll
-    for (int j = 0; j < M; ++j) m[j] = row ? sm.Quu[min(ri, j)][max(ri, j)] : 0.0;
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-      const double piv = bcast(m[j], j);
-      ok = ok && (piv > 0.0) && isfinite(piv);
-      const double inv = rsqrt_nr(piv);
-      const double ljj = piv * inv;
-      if (lane == 0) sm.Lqi[j] = inv;
-      const double lij = (lane == j) ? ljj : (lane > j && row ? m[j] * inv : 0.0);
-      m[j] = lij;
-#pragma unroll
-      for (int k = j + 1; k < M; ++k) m[k] -= lij * bcast(lij, k);
-    }
-    if (row)
-#pragma unroll
-      for (int j = 0; j < M; ++j) sm.Lq[ri][j] = m[j];
-    if constexpr (sizeof(R) == 4) {
-      // mixed form: the factor rounded to FP32 for the gain solves, in the
-      // storage of Q_uu (read above, not needed again)
-      float* lf = reinterpret_cast<float*>(&sm.Quu[0][0]);
-      if (row)
-#pragma unroll
-        for (int j = 0; j < M; ++j) lf[ri * (M + 1) + j] = float(m[j]);
-      wave_sync();  // the reciprocal pivots were stored by lane 0
-      if (lane < M) lf[M * (M + 1) + lane] = float(sm.Lqi[lane]);
-    }
-    if (lane == 0) sm.flag = ok ? 0 : 1;
+// Both by one wave.  factor_quu: Q_uu (rows on lanes 0..11; the pivot column
+// reaches the other lanes by row broadcasts, which the subtraction reads as an
+// operand) to its factor in R (the mixed form's gain solves run in FP32 on the
+// FP64 factor rounded to FP32, as in the lane kernels).
+__device__ __forceinline__ void row_fnma(double& m, double l, int k) {
+  asm("v_fmac_f64_dpp %0, -%1, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(m) : "v"(l), "n"(k));
+}
+template <int J>
+__device__ __forceinline__ double row_bcast(double v) {
+  return __builtin_bit_cast(double, dpp_update_i64(0L, __builtin_bit_cast(long, v), 0x150 + J, 0xF, 0xF, true));
+}
+template <int J, class R>
+__device__ __forceinline__ void factor_col(Smem<R>& sm, double (&m)[M], bool& ok, int lane) {
+  if constexpr (J < M) {
+    const double piv = row_bcast<J>(m[J]);
+    ok = ok && (piv > 0.0) && isfinite(piv);
+    const double inv = rsqrt_nr(piv);
+    const double ljj = piv * inv;
+    if (lane == 0) sm.Lri[J] = R(inv);
+    double lij = (lane == J) ? ljj : (lane > J && lane < M ? m[J] * inv : 0.0);
+    m[J] = lij;
+    // m[k] -= l_i l_k (the wait states before a DPP read of l)
+    asm("s_nop 1" : "+v"(lij));
+    if constexpr (J + 1 < M) row_fnma(m[J + 1 < M ? J + 1 : 0], lij, J + 1);
+    if constexpr (J + 2 < M) row_fnma(m[J + 2 < M ? J + 2 : 0], lij, J + 2);
+    if constexpr (J + 3 < M) row_fnma(m[J + 3 < M ? J + 3 : 0], lij, J + 3);
+    if constexpr (J + 4 < M) row_fnma(m[J + 4 < M ? J + 4 : 0], lij, J + 4);
+    if constexpr (J + 5 < M) row_fnma(m[J + 5 < M ? J + 5 : 0], lij, J + 5);
+    if constexpr (J + 6 < M) row_fnma(m[J + 6 < M ? J + 6 : 0], lij, J + 6);
+    if constexpr (J + 7 < M) row_fnma(m[J + 7 < M ? J + 7 : 0], lij, J + 7);
+    if constexpr (J + 8 < M) row_fnma(m[J + 8 < M ? J + 8 : 0], lij, J + 8);
+    if constexpr (J + 9 < M) row_fnma(m[J + 9 < M ? J + 9 : 0], lij, J + 9);
+    if constexpr (J + 10 < M) row_fnma(m[J + 10 < M ? J + 10 : 0], lij, J + 10);
+    if constexpr (J + 11 < M) row_fnma(m[J + 11 < M ? J + 11 : 0], lij, J + 11);
+    factor_col<J + 1, R>(sm, m, ok, lane);
   }
-  __syncthreads();
-  if (sm.flag) return false;
-  if constexpr (sizeof(R) == 4) {
-    // mixed form: the gains are stored in FP32, so their triangular solves run
-    // in FP32 on the FP64 factor rounded to FP32 (as in the lane kernels)
-    if (tid <= N) {
-      const float* lf = reinterpret_cast<const float*>(&sm.Quu[0][0]);
-      const float* lfi = lf + M * (M + 1);
-      float y[M];
+}
+template <class R>
+__device__ __forceinline__ void factor_quu(Smem<R>& sm, int lane_) {
+  const int lane = fresh(lane_);
+  const bool row = lane < M;
+  const int ri = row ? lane : 0;
+  double m[M];
 #pragma unroll
-      for (int i = 0; i < M; ++i) y[i] = tid < N ? sm.Qux[i][tid] : sm.Qu[i];
+  for (int j = 0; j < M; ++j) m[j] = row ? sm.Quu[min(ri, j)][max(ri, j)] : 0.0;
+  bool ok = true;
+  factor_col<0, R>(sm, m, ok, lane);
+  if (row)
 #pragma unroll
-      for (int i = 0; i < M; ++i) {
-        float v0 = y[i], v1 = 0.0f;
+    for (int j = 0; j < M; ++j) sm.Lr[ri][j] = R(m[j]);
+  if (lane == 0) sm.flag = ok ? 0 : 1;
+}
+
+// Column `lane` (< 38) of [K | k] from that of [Q_ux | Q_u], in registers;
+// a non-finite gain sets nonfin.
+template <class R>
+__device__ __forceinline__ void solve_gains(Smem<R>& sm, int lane_) {
+  const int lane = fresh(lane_);
+  if (lane > N) return;
+  R y[M];
 #pragma unroll
-        for (int k = 0; k < i; ++k) {
-          if (k & 1) v1 += lf[i * (M + 1) + k] * y[k];
-          else v0 -= lf[i * (M + 1) + k] * y[k];
-        }
-        y[i] = (v0 - v1) * lfi[i];
-      }
+  for (int i = 0; i < M; ++i) y[i] = lane < N ? sm.QuxT[lane][kq(i)] : sm.Qu[i];
+  R l[M][M];
 #pragma unroll
-      for (int i = M - 1; i >= 0; --i) {
-        float v0 = y[i], v1 = 0.0f;
+  for (int i = 1; i < M; ++i)
 #pragma unroll
-        for (int k = i + 1; k < M; ++k) {
-          if (k & 1) v1 += lf[k * (M + 1) + i] * y[k];
-          else v0 -= lf[k * (M + 1) + i] * y[k];
-        }
-        y[i] = (v0 - v1) * lfi[i];
-      }
-      bool fin = true;
+    for (int k = 0; k < i; ++k) l[i][k] = sm.Lr[i][k];
 #pragma unroll
-      for (int i = 0; i < M; ++i) {
-        fin = fin && isfinite(y[i]);
-        if (tid < N) sm.Kg[i][tid] = R(-y[i]);
-        else sm.kk[i] = R(-y[i]);
-      }
-      if (!fin) sm.flag = 2;
+  for (int i = 0; i < M; ++i) {
+    R v0 = y[i], v1 = R(0);
+#pragma unroll
+    for (int k = 0; k < i; ++k) {
+      if (k & 1) v1 += l[i][k] * y[k];
+      else v0 -= l[i][k] * y[k];
     }
-    __syncthreads();
-    return sm.flag == 0;
+    y[i] = (v0 - v1) * sm.Lri[i];
   }
-  if (tid <= N) {  // column tid of [Q_ux | Q_u]; the column lives in registers
-    double y[M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) y[i] = double(tid < N ? sm.Qux[i][tid] : sm.Qu[i]);
+  for (int i = M - 1; i >= 0; --i) {
+    R v0 = y[i], v1 = R(0);
 #pragma unroll
-    for (int i = 0; i < M; ++i) {
-      double v0 = y[i], v1 = 0.0;
-#pragma unroll
-      for (int k = 0; k < i; ++k) {
-        if (k & 1) v1 += sm.Lq[i][k] * y[k];
-        else v0 -= sm.Lq[i][k] * y[k];
-      }
-      y[i] = (v0 - v1) * sm.Lqi[i];
+    for (int k = i + 1; k < M; ++k) {
+      if (k & 1) v1 += l[k][i] * y[k];
+      else v0 -= l[k][i] * y[k];
     }
-#pragma unroll
-    for (int i = M - 1; i >= 0; --i) {
-      double v0 = y[i], v1 = 0.0;
-#pragma unroll
-      for (int k = i + 1; k < M; ++k) {
-        if (k & 1) v1 += sm.Lq[k][i] * y[k];
-        else v0 -= sm.Lq[k][i] * y[k];
-      }
-      y[i] = (v0 - v1) * sm.Lqi[i];
-    }
-    bool fin = true;
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      fin = fin && isfinite(y[i]);
-      if (tid < N) sm.Kg[i][tid] = R(-y[i]);
-      else sm.kk[i] = R(-y[i]);
-    }
-    if (!fin) sm.flag = 2;
+    y[i] = (v0 - v1) * sm.Lri[i];
   }
-  __syncthreads();
-  return sm.flag == 0;
+  bool fin = true;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    fin = fin && isfinite(y[i]);
+    if (lane < N) sm.KT[lane][kq(i)] = -y[i];
+    else sm.kk[i] = -y[i];
+  }
+  if (!fin) sm.nonfin = 1;
 }
 
 // ------------------------------------------------------------------ bounded control step (eq. 1)
-// FP64 storage of the bounded step inside PB (free once Q_uu is formed):
-// H = Q_uu [M][M + 1], then the reciprocal pivots of a face factor [M].
-template <class R>
-__device__ __forceinline__ double* box_H(Smem<R>& sm) {
-  return reinterpret_cast<double*>(&sm.PB[0][0]);
-}
-static_assert(sizeof(double) * (M * (M + 1) + M) <= sizeof(float) * N * LDB, "box step storage fits PB");
-
 // Wave-parallel Cholesky (rows on lanes, the pivot column broadcast from its
 // lane) of the face of H with the components in W held: their rows and
 // columns become identity.  Lane i < M keeps row i of the factor in f and
@@ -562,7 +545,7 @@ __device__ __forceinline__ double face_solve(const double (&f)[M], const double 
   return y;
 }
 
-// The control step under the bound (paper eq. 1) once gains() has formed the
+// The control step under the bound (paper eq. 1) once solve_gains has formed the
 // unconstrained gains: when the step k_k lies in the box [-umax - u_k,
 // umax - u_k] it stands (so a bound that never binds changes nothing).
 // Otherwise wave 0 minimises 0.5 d'Hd + Q_u'd over the box exactly in FP64 by
@@ -576,14 +559,14 @@ __device__ __forceinline__ double face_solve(const double (&f)[M], const double 
 // face's factor: K = -[face factor]^-1 Q_ux with the held rows of Q_ux zeroed.
 // Returns 0 or the status bit that freezes the instance.
 template <class R>
-__device__ uint32_t box_step(Smem<R>& sm, const WaveScratch<R>& w0, double umax, int tid) {
-  double* H = box_H(sm);
-  double* Li = H + M * (M + 1);
+__device__ uint32_t box_step(Smem<R>& sm, const R* uk, double umax, int tid) {
+  const double* H = &sm.Quu[0][0];
+  double* Li = sm.Li;
   if (tid < 64) {
     const int lane = tid;
     const bool row = lane < M;
     const int ri = row ? lane : 0;
-    const double u = double(w0.u[ri]);
+    const double u = double(uk[ri]);
     const double lo = -umax - u, hi = umax - u;
     const double kk = double(sm.kk[ri]);
     const bool inside = !row || (kk >= lo && kk <= hi);
@@ -682,7 +665,7 @@ __device__ uint32_t box_step(Smem<R>& sm, const WaveScratch<R>& w0, double umax,
     const unsigned W = sm.Hq_held;
     double y[M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) y[i] = ((W >> i) & 1u) ? 0.0 : double(sm.Qux[i][tid]);
+    for (int i = 0; i < M; ++i) y[i] = ((W >> i) & 1u) ? 0.0 : double(sm.QuxT[tid][kq(i)]);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
       double v = y[i];
@@ -700,8 +683,9 @@ __device__ uint32_t box_step(Smem<R>& sm, const WaveScratch<R>& w0, double umax,
     bool fin = true;
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      sm.Kg[i][tid] = R(-y[i]);
-      fin = fin && isfinite(sm.Kg[i][tid]);
+      const R kv = R(-y[i]);
+      sm.KT[tid][kq(i)] = kv;
+      fin = fin && isfinite(kv);
     }
     if (tid < M) fin = fin && isfinite(sm.kk[tid]);
     if (!fin) sm.flag = 2;
@@ -728,48 +712,60 @@ struct QW {  // workspace accessors (the lane schedule's slot-major layout)
 
 // ------------------------------------------------------------------ backward sweep
 // BOX: the bounded control step of eq. 1 (umax); mu: the Levenberg-Marquardt
-// shift of Q_uu (zero for the clipped form)
+// shift of Q_uu (zero for the clipped form).
+//
+// A step is a chain of four phases between barriers, each spread over the
+// four waves (16 x 16 tiles; all operands as rows in kpos order):
+//   1. (P [f_x | f_u])^T, wave w the columns of block w (three of f_x, one of
+//      f_u) against P's three row blocks; P's row 37 holds p, so the same
+//      tiles give f_x^T p and f_u^T p;
+//   2. waves 0..2: the Q_xx tiles (w, w), (w, w + 1) and the transpose of
+//      (w + 1, w), kept in registers, and Q_ux's tile of block w; wave 3: Q_uu
+//      and its factor, the phase's longest chain;
+//   3. wave 3: the gains; waves 0..2 put the next step's derivative block,
+//      which they loaded during phase 2, into the other buffer;
+//   4. waves 0..2: C = Q_xx + Q_ux^T K on their tiles and P = sym(C): a pair
+//      of tiles is symmetrised in registers, a diagonal tile through the
+//      wave's own scratch; wave 3: p and the gains' store.
+// Bound: this chain (latency of the dependent matrix instructions, of the
+// factor's twelve pivots and of LDS), of which two resident instances hide
+// each other's.  Before, with scalar operand loads under bounds checks and
+// Q_xx, C and its symmetrised form through LDS, a step took six barriers and
+// 1024 mixed instances 13.0 ms per solve, 100 in FP64 13.9; now 8.8 and 9.3 (a
+// step's phases take 2.2, 7.1, 2.9 and 2.7 thousand cycles).
 template <class R, bool BOX>
 __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restrict__ prm, const LaneState<R>& w, int s, int T,
                              int buf, R eps, int tid, R* __restrict__ blk, double mu, double umax) {
   using Q = QW<R>;
+  using V = typename MfAcc<R>::type;
+  constexpr int S = Stride<R>::k;
   const R dt = R(prm[O_DT]);
   const R wq = R(prm[O_WQ]), wv = R(prm[O_WV]), wu = R(prm[O_WU]), wT = R(prm[O_WT]);
   // terminal: P = clip(l_T,xx) (diagonal), p = l_T,x
-  for (int i = tid; i < N * LD; i += NT) (&sm.P[0][0])[i] = R(0);
+  for (int i = tid; i < (N + 1) * S; i += NT) (&sm.P[0][0])[i] = R(0);
   __syncthreads();
   if (tid < N) {
     const R xv = Q::xp(w, buf, T, s)[tid];
     const R wi = (tid < NQ ? wq : wv) * wT;
-    sm.p[tid] = R(2) * wi * (xv - sm.xnom[tid]);
-    sm.P[tid][tid] = dmax(R(2) * wi, eps);
+    sm.P[N][kpos(tid)] = R(2) * wi * (xv - sm.xnom[tid]);
+    sm.P[tid][kpos(tid)] = dmax(R(2) * wi, eps);
   }
   __syncthreads();
-  const int wid = tid >> 6, lane = tid & 63;
-  // Step kk's (x, u) go to the scratch of wave 2 + (kk & 1) (free between the
-  // derivative pre-passes) and its derivative block to A, Bm, by the threads
-  // from `first` on.  The first step of a chunk is staged by all threads after
-  // the pre-pass; every other step by waves 1..3 while wave 0 factors the
-  // previous step's Q_uu (A and Bm are not read again in a step once Q_uu is
-  // formed).
-  auto stage = [&](int kk, int first) {
-    const int t = tid - first, nt = NT - first;
-    if (t < 0) return;
-    WaveScratch<R>& sx = sm.wv[2 + (kk & 1)];
-    if (t < N) sx.x[t] = Q::xp(w, buf, kk, s)[t];
-    if (t < M) sx.u[t] = Q::up(w, buf, kk, s)[t];
-    const R* src = blk + ((T - 1 - kk) % CH) * DB;
-    for (int i = t; i < DB; i += nt) {
-      const int r = i / (N + M), c = i - r * (N + M);
-      const R v = src[i];
-      if (c < N) sm.A[r][c] = v;
-      else sm.Bm[r][c - N] = v;
-    }
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // derivative blocks are copied by 16-byte pieces
+  struct alignas(16) Piece { R v[16 / sizeof(R)]; };
+  constexpr int PR = KROW * int(sizeof(R)) / 16, NP = (N + M) * PR;  // pieces per row, per block
+  auto block_of = [&](int kk) { return blk + ((T - 1 - kk) % CH) * DB; };
+  auto put_piece = [&](int kk, int i, const Piece& v) {
+    const int r = i / PR, c = i - r * PR;
+    *reinterpret_cast<Piece*>(&sm.AT[kk & 1][r < N ? r : BROW + r - N][c * (16 / int(sizeof(R)))]) = v;
   };
+  constexpr int NS = NT - 64, PP = (NP + NS - 1) / NS;  // staging threads of a step, pieces of each
   for (int k = T - 1; k >= 0; --k) {
     const int q = (T - 1 - k) % CH;
-    WaveScratch<R>& sx = sm.wv[2 + (k & 1)];
+    const int cb = k & 1;
     if (q == 0) {
+      const int lane = fresh(tid & 63);
       // derivative blocks of the next CH steps, wave wid taking every fourth
       // step (they do not depend on P)
       WaveScratch<R>& wsw = sm.wv[wid];
@@ -782,83 +778,164 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
         wave_sync();
       }
       __syncthreads();
-      stage(k, 0);
+      const Piece* src = reinterpret_cast<const Piece*>(block_of(k));
+      for (int i = tid; i < NP; i += NT) put_piece(k, i, src[i]);
+      if (tid < N) sm.xs[cb][tid] = Q::xp(w, buf, k, s)[tid];
+      if (tid < M) sm.us[cb][tid] = Q::up(w, buf, k, s)[tid];
       __syncthreads();
     }
-    // PA = P A, PB = P B: nine 16 x 16 tiles of P A and three of P B; in the
-    // same phase Q_x = l_x + A^T p and Q_u = l_u + B^T p (p is replaced only
-    // after the gains) as four one-column tiles, the cost gradients (diagonal
-    // Hessians) added to their results: sixteen tiles, four per wave
-    for (int t = tid >> 6; t < 16; t += NW) {
-      if (t < 9)
-        mfma_tile<N, false, false>(&sm.PA[0][0], LD, &sm.P[0][0], LD, &sm.A[0][0], LD, (const R*)nullptr, 0, N, N,
-                                   (t / 3) * 16, (t % 3) * 16, tid & 63);
-      else if (t < 12)
-        mfma_tile<N, false, false>(&sm.PB[0][0], LDB, &sm.P[0][0], LD, &sm.Bm[0][0], LDB, (const R*)nullptr, 0, N, M,
-                                   (t - 9) * 16, 0, tid & 63);
-      else if (t < 15)
-        mfma_tile_out<N, true, false>(
-            [&](int i, int, R v) { sm.Qx[i] = R(2) * (i < NQ ? wq : wv) * (sx.x[i] - sm.xnom[i]) + v; },
-            &sm.A[0][0], LD, &sm.p[0], 1, N, 1, (t - 12) * 16, 0, tid & 63);
-      else
-        mfma_tile_out<N, true, false>([&](int i, int, R v) { sm.Qu[i] = R(2) * wu * sx.u[i] + v; }, &sm.Bm[0][0],
-                                      LDB, &sm.p[0], 1, M, 1, 0, 0, tid & 63);
+    // ---- phase 1
+    {
+      const int lane = fresh(tid & 63), li = lane & 15, lk = lane >> 4;
+      R at[10], pr[3][10];
+      ld_op(at, &sm.AT[cb][16 * wid + li][lk * KG]);
+#pragma unroll
+      for (int b = 0; b < 3; ++b) ld_op(pr[b], &sm.P[16 * b + li][lk * KG]);
+      V acc[3] = {};
+#pragma unroll
+      for (int t = 0; t < 10; ++t)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) acc[b] = mfma16(pr[b][t], at[t], acc[b]);
+      R* dst = sm.PAT[16 * wid + li];
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = 16 * b + MfAcc<R>::row(lk, r);
+          dst[kpos(i)] = i < N ? acc[b][r] : R(0);
+        }
+      // row 37 of the products
+      if (lk == 1) {
+        const int j = wid < 3 ? 16 * wid + li : N + li;
+        if (wid < 3 ? j < N : li < M) sm.Qg[j] = acc[2][1];
+      }
     }
     __syncthreads();
-    // Q_xx = clip(l_xx) + A^T (P A) into P, Q_ux = B^T (P A): twelve tiles; Q_uu =
-    // clip(l_uu) + B^T (P B) (+ mu I, the Levenberg-Marquardt shift, zero
-    // otherwise: adding it changes no bit) in FP64 from a thirteenth
-    for (int t = tid >> 6; t < 13; t += NW) {
-      if (t < 9)
-        mfma_tile<N, true, false>(&sm.P[0][0], LD, &sm.A[0][0], LD, &sm.PA[0][0], LD, (const R*)nullptr, 0, N, N,
-                                  (t / 3) * 16, (t % 3) * 16, tid & 63);
-      else if (t < 12)
-        mfma_tile<N, true, false>(&sm.Qux[0][0], LD, &sm.Bm[0][0], LDB, &sm.PA[0][0], LD, (const R*)nullptr, 0, M, N,
-                                  0, (t - 9) * 16, tid & 63);
-      else
-        mfma_tile_out<N, true, false>(
-            [&](int i, int j, R v) {
-              double q = double(v) + (i == j ? double(dmax(R(2) * wu, eps)) : 0.0);
-              if (i == j) q += mu;
-              sm.Quu[i][j] = q;
-            },
-            &sm.Bm[0][0], LDB, &sm.PB[0][0], LDB, M, M, 0, 0, tid & 63);
+    // ---- phase 2
+    const int lane = fresh(tid & 63), li = lane & 15, lk = lane >> 4, ltid = 64 * wid + lane;
+    V cxy = {}, cyx = {}, cd = {};  // tiles (x, y), (y, x)^T and (x, x) of Q_xx
+    const int x0 = 16 * wid, y0 = wid == 2 ? 0 : 16 * (wid + 1);
+    const bool ahead = k >= 1 && q + 1 < CH;
+    Piece nxt[PP];
+    R xn = R(0), un = R(0);
+    if (wid < 3) {
+      if (ahead) {
+        const Piece* src = reinterpret_cast<const Piece*>(block_of(k - 1));
+#pragma unroll
+        for (int i = 0; i < PP; ++i)
+          if (ltid + i * NS < NP) nxt[i] = src[ltid + i * NS];
+        if (ltid < N) xn = Q::xp(w, buf, k - 1, s)[ltid];
+        if (ltid < M) un = Q::up(w, buf, k - 1, s)[ltid];
+      }
+      R ax[10], ay[10], px[10], py[10], bt[10];
+      ld_op(ax, &sm.AT[cb][x0 + li][lk * KG]);
+      ld_op(px, &sm.PAT[x0 + li][lk * KG]);
+      ld_op(bt, &sm.AT[cb][BROW + li][lk * KG]);
+      ld_op(ay, &sm.AT[cb][y0 + li][lk * KG]);
+      ld_op(py, &sm.PAT[y0 + li][lk * KG]);
+      V cu = {};
+#pragma unroll
+      for (int t = 0; t < 10; ++t) {
+        cu = mfma16(bt[t], px[t], cu);
+        cd = mfma16(ax[t], px[t], cd);
+        cxy = mfma16(ax[t], py[t], cxy);
+        cyx = mfma16(px[t], ay[t], cyx);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        sm.QuxT[x0 + li][kq(MfAcc<R>::row(lk, r))] = cu[r];
+        // the clipped diagonal Hessian
+        const int i = x0 + MfAcc<R>::row(lk, r);
+        if (MfAcc<R>::row(lk, r) == li && i < N) cd[r] += dmax(R(2) * (i < NQ ? wq : wv), eps);
+      }
+    } else {
+      // Q_uu = clip(l_uu) + B^T (P B) (+ mu I, the Levenberg-Marquardt shift,
+      // zero otherwise: adding it changes no bit) in FP64
+      R bt[10], pb[10];
+      ld_op(bt, &sm.AT[cb][BROW + li][lk * KG]);
+      ld_op(pb, &sm.PAT[BROW + li][lk * KG]);
+      V cq = {};
+#pragma unroll
+      for (int t = 0; t < 10; ++t) cq = mfma16(bt[t], pb[t], cq);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = MfAcc<R>::row(lk, r);
+        if (i < M && li < M) {
+          double v = double(cq[r]) + (i == li ? double(dmax(R(2) * wu, eps)) : 0.0);
+          if (i == li) v += mu;
+          sm.Quu[i][li] = v;
+        }
+      }
+      if (lane < M) sm.Qu[lane] = R(2) * wu * sm.us[cb][lane] + sm.Qg[N + lane];
+      if (lane == 0) sm.nonfin = 0;
+      wave_sync();
+      factor_quu(sm, lane);
     }
     __syncthreads();
-    if (tid < N) sm.P[tid][tid] += dmax(R(2) * (tid < NQ ? wq : wv), eps);
-    if constexpr (BOX) {
-      // Q_uu for the bounded step (gains() reuses its storage in the mixed form)
-      if (tid < M * M) box_H(sm)[(tid / M) * (M + 1) + tid % M] = sm.Quu[tid / M][tid % M];
-      __syncthreads();
+    if (sm.flag) return ST_CHOL_FAIL;
+    // ---- phase 3
+    if (wid == 3) {
+      solve_gains(sm, lane);
+    } else if (ahead) {
+#pragma unroll
+      for (int i = 0; i < PP; ++i)
+        if (ltid + i * NS < NP) put_piece(k - 1, ltid + i * NS, nxt[i]);
+      if (ltid < N) sm.xs[cb ^ 1][ltid] = xn;
+      if (ltid < M) sm.us[cb ^ 1][ltid] = un;
     }
-    if (!gains(sm, tid, [&] {
-          if (k >= 1 && q + 1 < CH) stage(k - 1, 64);
-        }))
-      return sm.flag == 1 ? ST_CHOL_FAIL : ST_NONFINITE;
+    __syncthreads();
+    if (sm.nonfin) return ST_NONFINITE;
     if constexpr (BOX) {
-      const uint32_t b = box_step(sm, sx, umax, tid);
+      const uint32_t b = box_step(sm, sm.us[cb], umax, tid);
       if (b) return b;
     }
-    // store the gains
-    {
+    // ---- phase 4: C = Q_xx + Q_ux^T K, P = sym(C), p = Q_x + Q_ux^T k
+    if (wid < 3) {
+      R qx[3], qy[3], kx[3], ky[3];
+      ld_op12(qx, &sm.QuxT[x0 + li][lk * 4]);
+      ld_op12(kx, &sm.KT[x0 + li][lk * 4]);
+      ld_op12(qy, &sm.QuxT[y0 + li][lk * 4]);
+      ld_op12(ky, &sm.KT[y0 + li][lk * 4]);
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        cd = mfma16(qx[t], kx[t], cd);
+        cxy = mfma16(qx[t], ky[t], cxy);
+        cyx = mfma16(kx[t], qy[t], cyx);
+      }
+      R* sc = sm.PAT[x0];  // the wave's sixteen rows
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[MfAcc<R>::row(lk, r) * S + li] = cd[r];
+      const int j = y0 + li;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = x0 + MfAcc<R>::row(lk, r);
+        if (i < N && j < N) {
+          const R v = R(0.5) * (cxy[r] + cyx[r]);
+          sm.P[i][kpos(j)] = v;
+          sm.P[j][kpos(i)] = v;
+        }
+      }
+      wave_sync();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = MfAcc<R>::row(lk, r);
+        const R v = R(0.5) * (cd[r] + sc[li * S + i]);
+        if (x0 + i < N && x0 + li < N) sm.P[x0 + i][kpos(x0 + li)] = v;
+      }
+    } else {
       R* dK = Q::Kp(w, k, s);
-      for (int i = tid; i < M * N; i += NT) dK[i] = sm.Kg[i / N][i % N];
-      if (tid < M) Q::kp(w, k, s)[tid] = sm.kk[tid];
-    }
-    // C = Q_xx + Q_ux^T K into PA, p = Q_x + Q_ux^T k
-    for (int t = tid >> 6; t < 9; t += NW)
-      mfma_tile<M, true, false>(&sm.PA[0][0], LD, &sm.Qux[0][0], LD, &sm.Kg[0][0], LD, &sm.P[0][0], LD, N, N,
-                                (t / 3) * 16, (t % 3) * 16, tid & 63);
-    if (tid < N) {
-      R v = sm.Qx[tid];
-      for (int t = 0; t < M; ++t) v += sm.Qux[t][tid] * sm.kk[t];
-      sm.p[tid] = v;
-    }
-    __syncthreads();
-    // P = sym(C)
-    for (int idx = tid; idx < N * N; idx += NT) {
-      const int i = idx / N, j = idx % N;
-      sm.P[i][j] = R(0.5) * (sm.PA[i][j] + sm.PA[j][i]);
+#pragma unroll
+      for (int e = 0; e < (M * N + 63) / 64; ++e) {
+        const int i = e * 64 + lane, t = i / N;
+        if (i < M * N) dK[i] = sm.KT[i - t * N][kq(t)];
+      }
+      if (lane < M) Q::kp(w, k, s)[lane] = sm.kk[lane];
+      if (lane < N) {
+        R v = R(2) * (lane < NQ ? wq : wv) * (sm.xs[cb][lane] - sm.xnom[lane]) + sm.Qg[lane];
+#pragma unroll
+        for (int t = 0; t < M; ++t) v += sm.QuxT[lane][kq(t)] * sm.kk[t];
+        sm.P[N][kpos(lane)] = v;
+      }
     }
     __syncthreads();
   }
@@ -871,8 +948,9 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
 // With BOX the trial's controls are clamped into [-umax, umax] (eq. 1).
 template <class R, bool BOX>
 __device__ __forceinline__ double wave_trial(Smem<R>& sm, const double* __restrict__ prm, const LaneState<R>& w, int s, int T,
-                             int buf, R alpha, double Jcur, bool write, int lane, int wid, int& steps, R umax) {
+                             int buf, R alpha, double Jcur, bool write, int lane_, int wid, int& steps, R umax) {
   using Q = QW<R>;
+  const int lane = fresh(lane_);
   WaveScratch<R>& ws = sm.wv[wid];
   const R dt = R(prm[O_DT]);
   const int nb = buf ^ 1;
@@ -886,6 +964,7 @@ __device__ __forceinline__ double wave_trial(Smem<R>& sm, const double* __restri
   const int c = lane >> 2, part = lane & 3;
   R xq = R(0), uq = R(0), kq = R(0), Kq[KQ];
   auto load = [&](int k) {
+    const int lane = fresh(lane_), c = lane >> 2, part = lane & 3;
     if (lane < N) xq = Q::xp(w, buf, k, s)[lane];
     if (c < M) {
       const R* Kr = Q::Kp(w, k, s) + c * N;
@@ -899,6 +978,7 @@ __device__ __forceinline__ double wave_trial(Smem<R>& sm, const double* __restri
   };
   load(0);
   for (int k = 0; k < T; ++k) {
+    const int lane = fresh(lane_), c = lane >> 2, part = lane & 3;
     const R xk = xq, uk = uq, kk = kq;
     R Kc[KQ];
 #pragma unroll
@@ -1026,7 +1106,7 @@ __global__ void __launch_bounds__(NT, OCC) quad_iterate(const double* __restrict
   const int s = slots ? slots[g] : g;
   uint32_t st = w.status[s];
   if (st) return;  // uniform over the workgroup
-  const int lane = tid & 63, wid = tid >> 6;
+  const int lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   stage_constants(sm, prm, tid);
   __syncthreads();
   const int T = w.T[s];

@@ -4,9 +4,10 @@ split) on the same instances, at horizons around the chunk edges."""
 import numpy as np
 import pytest
 
+from oracle import oracle as orc
 from paper_2602_19699_amd import inputs as I
 
-from gpu_helpers import gpu_solve
+from gpu_helpers import gpu_solve, oracle_opts, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +69,23 @@ def test_trial_budget_of_any_size(ctx, kind, trials):
     ref = gpu_solve(ctx, kind, p, x0, 50, group_lanes=1, **o)
     for g in (2, 4, 8, 16):
         _equal(ref, gpu_solve(ctx, kind, p, x0, 50, group_lanes=g, **o), [k for k in FIELDS if k != "work"], f"{g}")
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("form", [{}, {"u_max": 6.0}, {"regularization": 1}], ids=["clip", "bound", "lm"])
+def test_quadruped_chunk_edges(ctx, prec, form):
+    # horizons around the sweep's 12-step chunks of derivative blocks, a bad
+    # and a non-finite instance among them, against the FP64 oracle
+    T = np.array([1, 2, 11, 12, 13, 23, 24, 25, 36, 37, 0, 5], np.int32)
+    p = I.quad_params(0)
+    x0 = I.quad_x0(len(T), p, 91)
+    x0[11, 20] = np.nan
+    o = dict(max_iter=6, stop_mode=1, rtol=1e-10 if prec == 0 else 1e-4, **form)
+    g = gpu_solve(ctx, I.SYS_QUAD_SYNTH, p, x0, 37, T=T, precision=prec, **o)
+    r = orc.solve_batch(I.SYS_QUAD_SYNTH, p, x0[:10], 37, T=T[:10],
+                        opts=oracle_opts(**{**o, "rtol": 1e-10}))
+    assert np.all(rel(g["J"][:10], r.J) <= (1e-9 if prec == 0 else 1e-4))
+    assert g["status"][10] == 32 and g["status"][11] == 8
+    for wg in (1, 2):  # either schedule
+        _equal(g, gpu_solve(ctx, I.SYS_QUAD_SYNTH, p, x0, 37, T=T, precision=prec, wg_per_cu=wg, **o),
+               [k for k in FIELDS if g[k] is not None], f"wg_per_cu={wg}")
