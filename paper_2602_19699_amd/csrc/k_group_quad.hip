@@ -45,25 +45,26 @@ constexpr int CH = 12;                  // steps per chunk of precomputed deriva
 constexpr int O_DT = 0, O_WU = 1, O_WT = 2, O_WQ = 3, O_WV = 4, O_M0 = 5, O_W1 = O_M0 + 324,
               O_W2 = O_W1 + 324, O_E = O_W2 + 324, O_XN = O_E + 18, NPRM = O_XN + 37;
 
+constexpr int LR = 20;  // row stride of 18-wide LDS matrices: whole 16-byte pieces
 template <class R>
 struct WaveScratch {
-  R L[NV][NV + 1];  // Cholesky factor of M(q), lower, row-major
-  R Li[NV];         // reciprocals of its diagonal
-  R x[LD];          // state of this wave's rollout
-  R xn[LD];         // next state
-  R u[16];          // control
+  alignas(16) R L[NV][LR];  // Cholesky factor of M(q), lower, row-major, zero above
+  alignas(16) R Li[LR];     // reciprocals of its diagonal
+  alignas(16) R s[LR], c[LR];  // sin, cos of q[0:18]
+  R x[LD];                  // state of this wave's rollout
+  R xn[LD];                 // next state
+  R u[16];                  // control
   R dx[LD];
-  R s[NV], c[NV];   // sin, cos of q[0:18]
-  R a[NV];          // acceleration M^-1 (S u - b)
-  R w2c[NV];        // W2 cos q
+  R a[NV];                  // acceleration M^-1 (S u - b)
+  R w2c[NV];                // W2 cos q
 };
 
 template <class R>
 struct Smem {
   using real = R;
-  R M0[NV][NV + 1];
-  R W1[NV][NV + 1];
-  R W2[NV][NV + 1];
+  alignas(16) R M0[NV][LR];
+  alignas(16) R W1[NV][LR];
+  alignas(16) R W2[NV][LR];
   R e[NV];
   R xnom[LD];
   alignas(16) R P[48][Stride<R>::k];       // value Hessian (operand rows; symmetric), row 37: its gradient p
@@ -92,9 +93,9 @@ struct Smem {
 template <class R, int NWV>
 struct WaveSmem {
   using real = R;
-  R M0[NV][NV + 1];
-  R W1[NV][NV + 1];
-  R W2[NV][NV + 1];
+  alignas(16) R M0[NV][LR];
+  alignas(16) R W1[NV][LR];
+  alignas(16) R W2[NV][LR];
   R e[NV];
   R xnom[LD];
   R p[LD];  // the finalize's costate
@@ -142,10 +143,41 @@ __device__ __forceinline__ double bcast(double v, int j) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// The value of the lane whose number differs in bit `O`, given that the lanes
+// that differ in higher bits hold the same value already (a sum over the wave
+// from the highest bit down): register swaps between half waves and rows, then
+// rotations within a row (rotating by 4 reaches lane ^ 4 or its copy at ^ 8).
+template <int O>
+__device__ __forceinline__ int lane_other(int v, int lane) {
+  if constexpr (O == 32) {
+    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return lane & 32 ? p[0] : p[1];
+  } else if constexpr (O == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return lane & 16 ? p[0] : p[1];
+  } else {
+    constexpr int ctrl = O == 8 ? 0x128 : (O == 4 ? 0x124 : (O == 2 ? 0x4E : 0xB1));
+    return __builtin_amdgcn_mov_dpp(v, ctrl, 0xF, 0xF, true);
+  }
+}
+template <int O>
+__device__ __forceinline__ float lane_other(float v, int lane) {
+  return __int_as_float(lane_other<O>(__float_as_int(v), lane));
+}
+template <int O>
+__device__ __forceinline__ double lane_other(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = unsigned(lane_other<O>(int(b), lane)), hi = unsigned(lane_other<O>(int(b >> 32), lane));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 template <class R>
-__device__ __forceinline__ R wave_sum(R v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+__device__ __forceinline__ R wave_sum(R v, int lane) {
+  v += lane_other<32>(v, lane);
+  v += lane_other<16>(v, lane);
+  v += lane_other<8>(v, lane);
+  v += lane_other<4>(v, lane);
+  v += lane_other<2>(v, lane);
+  v += lane_other<1>(v, lane);
   return v;
 }
 
@@ -164,84 +196,126 @@ __device__ __forceinline__ void stage_constants(S& sm, const double* __restrict_
 }
 
 // ------------------------------------------------------------------ wave-level dynamics
+// an 18-wide row (or vector) in LDS, by 16-byte pieces
+template <class R>
+__device__ __forceinline__ void ld_row(R (&v)[NV], const R* p) {
+  struct alignas(16) Piece { R v[16 / sizeof(R)]; };
+  constexpr int E = 16 / int(sizeof(R));
+#pragma unroll
+  for (int i = 0; i < NV; i += E) {
+    const Piece q = *reinterpret_cast<const Piece*>(p + i);
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+      if (i + j < NV) v[i + j] = q.v[j];
+  }
+}
+template <class R>
+__device__ __forceinline__ void st_row(R* p, const R (&v)[NV]) {
+  struct alignas(16) Piece { R v[16 / sizeof(R)]; };
+  constexpr int E = 16 / int(sizeof(R));
+#pragma unroll
+  for (int i = 0; i < NV; i += E) {
+    Piece q;
+#pragma unroll
+    for (int j = 0; j < E; ++j) q.v[j] = i + j < NV ? v[i + j < NV ? i + j : 0] : R(0);
+    *reinterpret_cast<Piece*>(p + i) = q;
+  }
+}
+// one step of the forward (lanes past j) and backward (lanes before j)
+// substitution, entry j of the right-hand side in lane j: without branches,
+// which the chain of eighteen would wait on one by one
+template <class R>
+__device__ __forceinline__ R forward_step(R y, R l, R inv, int j, int lane) {
+  const R yj = bcast(y, j) * inv;
+  const R r = y - l * yj;
+  return lane == j ? yj : (lane > j ? r : y);
+}
+template <class R>
+__device__ __forceinline__ R backward_step(R y, R l, R inv, int j, int lane) {
+  const R zj = bcast(y, j) * inv;
+  const R r = y - l * zj;
+  return lane == j ? zj : (lane < j ? r : y);
+}
+
 // One semi-implicit Euler step for wave scratch ws: reads ws.x and ws.u,
-// writes ws.xn; leaves L (factor of M), a, sin/cos and W2 cos q in ws.
+// writes ws.xn; leaves L (factor of M), a, sin/cos and W2 cos q in ws.  A
+// serial chain (eighteen pivots, eighteen entries of the back substitution;
+// the forward one runs along with the factor); everything a lane needs of LDS
+// is loaded in wide pieces ahead of the chains.  A step of a line-search trial
+// takes 9.3 thousand cycles alone on its SIMD (17.9 with a branch per entry,
+// single loads inside the chains and shuffle sums); solve of 1024 mixed
+// instances 8.8 -> 6.5 ms, of 100 in FP64 9.3 -> 7.2 ms.
 template <class R, class S>
 __device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, int lane_) {
   const int lane = fresh(lane_);
-  if (lane < NV) {
-    R sn, cs;
-    dsincos_lib(ws.x[lane], &sn, &cs);
+  const bool row = lane < NV;
+  const int ri = row ? lane : 0;
+  R m[NV], w1[NV], w2[NV];
+  ld_row(m, sm.M0[ri]);
+  ld_row(w1, sm.W1[ri]);
+  ld_row(w2, sm.W2[ri]);
+  const R xq = ws.x[ri], xv = ws.x[NQ + ri], er = sm.e[ri], x18 = ws.x[NV];
+  const R ua = ws.u[ri >= 6 ? ri - 6 : 0];
+  R sn = R(0);
+  if (row) {
+    R cs;
+    dsincos_lib(xq, &sn, &cs);
     ws.s[lane] = sn;
     ws.c[lane] = cs;
   }
   wave_sync();
-  const bool row = lane < NV;
-  const int ri = row ? lane : 0;
+  // bias forces and right-hand side r = S u - b
+  R y = R(0);
+  {
+    R sv[NV], cv[NV], b1 = R(0), b2 = R(0);
+    ld_row(sv, ws.s);
+    ld_row(cv, ws.c);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      b1 += w1[j] * sv[j];
+      b2 += w2[j] * cv[j];
+    }
+    const R b = b1 + b2 * xv;
+    if (row) {
+      ws.w2c[ri] = b2;
+      y = (ri >= 6 ? ua : R(0)) - b;
+    }
+  }
   // M = A^T A + diag(1 + 0.1 sin q); Cholesky with the rows on lanes, the
-  // pivot column broadcast from its lane
-  R m[NV];
+  // pivot column broadcast from its lane, and L z = r along with it
+  {
+    const R d = R(1) + R(0.1) * sn;
 #pragma unroll
-  for (int j = 0; j < NV; ++j) m[j] = row ? sm.M0[ri][j] : R(0);
-#pragma unroll
-  for (int j = 0; j < NV; ++j)
-    if (j == lane) m[j] += R(1) + R(0.1) * ws.s[ri];
+    for (int j = 0; j < NV; ++j) m[j] = j == lane ? m[j] + d : m[j];
+  }
+  R inv[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
     const R piv = bcast(m[j], j);
-    const R inv = rsqrt_nr(piv);
-    const R ljj = piv * inv;
-    if (lane == 0) ws.Li[j] = inv;
-    const R lij = (lane == j) ? ljj : (lane > j && row ? m[j] * inv : R(0));
+    inv[j] = rsqrt_nr(piv);
+    const R ljj = piv * inv[j];
+    const R lij = (lane == j) ? ljj : (lane > j && row ? m[j] * inv[j] : R(0));
     m[j] = lij;
 #pragma unroll
-    for (int k = j + 1; k < NV; ++k) {
-      const R lkj = bcast(lij, k);
-      m[k] -= lij * lkj;
-    }
+    for (int k = j + 1; k < NV; ++k) m[k] -= lij * bcast(lij, k);
+    y = forward_step(y, lij, inv[j], j, lane);
   }
-  if (row)
-#pragma unroll
-    for (int j = 0; j < NV; ++j)
-      if (j <= lane) ws.L[ri][j] = m[j];
-  // bias forces and right-hand side r = S u - b
-  R y = R(0);
-  if (row) {
-    R b1 = R(0), b2 = R(0);
-#pragma unroll 3
-    for (int j = 0; j < NV; ++j) {
-      b1 += sm.W1[ri][j] * ws.s[j];
-      b2 += sm.W2[ri][j] * ws.c[j];
-    }
-    ws.w2c[ri] = b2;
-    const R b = b1 + b2 * ws.x[NQ + ri];
-    y = (ri >= 6 ? ws.u[ri - 6] : R(0)) - b;
-  }
+  if (row) st_row(ws.L[ri], m);
+  if (lane == 0) st_row(ws.Li, inv);
   wave_sync();
-  // L z = r (rows on lanes)
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const R yj = bcast(y, j) * ws.Li[j];
-    if (lane == j) y = yj;
-    else if (lane > j) y -= m[j] * yj;
-  }
   // L^T a = z
 #pragma unroll
-  for (int j = NV - 1; j >= 0; --j) {
-    const R zj = bcast(y, j) * ws.Li[j];
-    if (lane == j) y = zj;
-    else if (lane < j) y -= ws.L[j][ri] * zj;
-  }
-  R ev = R(0);
+  for (int j = 0; j < NV; ++j) m[j] = ws.L[j][ri];
+#pragma unroll
+  for (int j = NV - 1; j >= 0; --j) y = backward_step(y, m[j], inv[j], j, lane);
+  const R vn = xv + dt * y;
+  const R ev = wave_sum(row ? er * vn : R(0), lane);
   if (row) {
     ws.a[ri] = y;
-    const R vn = ws.x[NQ + ri] + dt * y;
     ws.xn[NQ + ri] = vn;
-    ws.xn[ri] = ws.x[ri] + dt * vn;
-    ev = sm.e[ri] * vn;
+    ws.xn[ri] = xq + dt * vn;
   }
-  ev = wave_sum(ev);
-  if (lane == 0) ws.xn[NV] = ws.x[NV] + dt * ev;
+  if (lane == 0) ws.xn[NV] = x18 + dt * ev;
   wave_sync();
 }
 
@@ -258,7 +332,7 @@ __device__ __forceinline__ R wave_cost(const S& sm, const R* x, const R* u, cons
     const R uu = u[lane - N];
     v = R(prm[O_WU]) * uu * uu;
   }
-  return wave_sum(v);
+  return wave_sum(v, lane);
 }
 
 // ------------------------------------------------------------------ MFMA tiles
@@ -338,40 +412,44 @@ __device__ __forceinline__ void wave_jac(const Smem<R>& sm, const WaveScratch<R>
                                          R* __restrict__ dst) {
   const int lane = fresh(lane_);
   if (lane < 48) {
-    const int c = lane;
-    R y[NV];
+    const int c = lane, cq = c < NV ? c : 0;
+    R y[NV], av[NV], w2c[NV], l[NV][NV], li[NV];
+    const R sc = ws.s[cq], cc = ws.c[cq];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      R v;
-      if (c < NV) {
-        v = -(sm.W1[i][c] * ws.c[c] - ws.x[NQ + i] * sm.W2[i][c] * ws.s[c]);
-        if (i == c) v -= R(0.1) * ws.c[i] * ws.a[i];
-      } else if (c < 2 * NV) {
-        v = (c - NV == i) ? -ws.w2c[i] : R(0);
-      } else {
-        v = (c - 2 * NV + 6 == i) ? R(1) : R(0);
-      }
-      y[i] = v;
+      av[i] = ws.a[i];
+      w2c[i] = ws.w2c[i];
     }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      R v = -(sm.W1[i][cq] * cc - ws.x[NQ + i] * sm.W2[i][cq] * sc);
+      if (i == c) v -= R(0.1) * ws.c[i] * av[i];
+      const R vv = (c - NV == i) ? -w2c[i] : R(0);
+      const R vu = (c - 2 * NV + 6 == i) ? R(1) : R(0);
+      y[i] = c < NV ? v : (c < 2 * NV ? vv : vu);
+    }
+    ld_row(li, ws.Li);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) ld_row(l[i], ws.L[i]);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       R v0 = y[i], v1 = R(0);
 #pragma unroll
       for (int k = 0; k < i; ++k) {
-        if (k & 1) v1 += ws.L[i][k] * y[k];
-        else v0 -= ws.L[i][k] * y[k];
+        if (k & 1) v1 += l[i][k] * y[k];
+        else v0 -= l[i][k] * y[k];
       }
-      y[i] = (v0 - v1) * ws.Li[i];
+      y[i] = (v0 - v1) * li[i];
     }
 #pragma unroll
     for (int i = NV - 1; i >= 0; --i) {
       R v0 = y[i], v1 = R(0);
 #pragma unroll
       for (int k = i + 1; k < NV; ++k) {
-        if (k & 1) v1 += ws.L[k][i] * y[k];
-        else v0 -= ws.L[k][i] * y[k];
+        if (k & 1) v1 += l[k][i] * y[k];
+        else v0 -= l[k][i] * y[k];
       }
-      y[i] = (v0 - v1) * ws.Li[i];
+      y[i] = (v0 - v1) * li[i];
     }
     // d v+_i / d (x, u)_col = [col is the velocity column i] + dt y_i; rows:
     // v+ (19..36), q+ = q + dt v+ (0..17), q_18+ = q_18 + dt e . v+
@@ -993,8 +1071,8 @@ __device__ __forceinline__ double wave_trial(Smem<R>& sm, const double* __restri
         for (int q = 0; q < KQ; ++q)
           if (part + 4 * q < N) acc += Kc[q] * ws.dx[part + 4 * q];
       }
-      acc += __shfl_xor(acc, 1, 64);
-      acc += __shfl_xor(acc, 2, 64);
+      acc += lane_other<1>(acc, lane);
+      acc += lane_other<2>(acc, lane);
       if (c < M && part == 0) {
         const R v = uk + alpha * kk + acc;
         ws.u[c] = BOX ? clamp_nan(v, umax) : v;
@@ -1332,18 +1410,15 @@ __global__ void __launch_bounds__(NT, 2) quad_final(const double* __restrict__ p
           WaveScratch<R>& ws = sm.wv[q];
           // nu = M^-1 mu: L z = mu, then L^T nu = z (rows on lanes)
           R y = row ? sm.p[NQ + ri] + dt * (sm.p[ri] + sm.e[ri] * sm.p[NV]) : R(0);
+          R l[NV], lt[NV], inv[NV];
+          ld_row(l, ws.L[ri]);
+          ld_row(inv, ws.Li);
 #pragma unroll
-          for (int j = 0; j < NV; ++j) {
-            const R yj = bcast(y, j) * ws.Li[j];
-            if (lane == j) y = yj;
-            else if (lane > j) y -= ws.L[ri][j] * yj;
-          }
+          for (int j = 0; j < NV; ++j) lt[j] = ws.L[j][ri];
 #pragma unroll
-          for (int j = NV - 1; j >= 0; --j) {
-            const R zj = bcast(y, j) * ws.Li[j];
-            if (lane == j) y = zj;
-            else if (lane < j) y -= ws.L[j][ri] * zj;
-          }
+          for (int j = 0; j < NV; ++j) y = forward_step(y, l[j], inv[j], j, lane);
+#pragma unroll
+          for (int j = NV - 1; j >= 0; --j) y = backward_step(y, lt[j], inv[j], j, lane);
           if (row) ws.dx[ri] = y;
           wave_sync();
           R ln = R(0);
@@ -1351,7 +1426,7 @@ __global__ void __launch_bounds__(NT, 2) quad_final(const double* __restrict__ p
             ln = R(2) * (lane < NQ ? wq : wv) * (ws.x[lane] - sm.xnom[lane]);
             if (lane < NV) {
               R g1 = R(0), g2 = R(0);
-#pragma unroll 6
+#pragma unroll
               for (int i = 0; i < NV; ++i) {
                 g1 += sm.W1[i][lane] * ws.dx[i];
                 g2 += sm.W2[i][lane] * (ws.dx[i] * ws.x[NQ + i]);
