@@ -72,7 +72,7 @@ struct Smem {
   alignas(16) R PAT[64][Stride<R>::k];     // (P [f_x | f_u])^T, the same rows; scratch of the update
   alignas(16) R QuxT[48][SQ], KT[48][SQ];  // Q_ux^T and the feedback gain's transpose (places kq)
   alignas(16) R Lr[M][16];                 // factor of Q_uu in R
-  R Lri[M];                                // reciprocals of its diagonal
+  alignas(16) R Lri[M];                    // reciprocals of its diagonal
   R Qg[N + M];                             // f_x^T p, f_u^T p
   R xs[2][LD], us[2][16];                  // state and control of this and the next step
   R Qu[16], kk[16];
@@ -117,6 +117,14 @@ __device__ __forceinline__ void wave_sync() {
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
+}
+
+// c ? a : b with both values formed first: left to itself the compiler turns
+// a chain of lane selects into branches around the arithmetic of each
+template <class R>
+__device__ __forceinline__ R pick(bool c, R a, R b) {
+  asm("" : "+v"(a), "+v"(b));
+  return c ? a : b;
 }
 
 // value of v in lane j (j uniform), read through a scalar register
@@ -227,14 +235,12 @@ __device__ __forceinline__ void st_row(R* p, const R (&v)[NV]) {
 template <class R>
 __device__ __forceinline__ R forward_step(R y, R l, R inv, int j, int lane) {
   const R yj = bcast(y, j) * inv;
-  const R r = y - l * yj;
-  return lane == j ? yj : (lane > j ? r : y);
+  return pick(lane == j, yj, pick(lane > j, y - l * yj, y));
 }
 template <class R>
 __device__ __forceinline__ R backward_step(R y, R l, R inv, int j, int lane) {
   const R zj = bcast(y, j) * inv;
-  const R r = y - l * zj;
-  return lane == j ? zj : (lane < j ? r : y);
+  return pick(lane == j, zj, pick(lane < j, y - l * zj, y));
 }
 
 // One semi-implicit Euler step for wave scratch ws: reads ws.x and ws.u,
@@ -286,7 +292,7 @@ __device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, 
   {
     const R d = R(1) + R(0.1) * sn;
 #pragma unroll
-    for (int j = 0; j < NV; ++j) m[j] = j == lane ? m[j] + d : m[j];
+    for (int j = 0; j < NV; ++j) m[j] = pick(j == lane, m[j] + d, m[j]);
   }
   R inv[NV];
 #pragma unroll
@@ -294,7 +300,7 @@ __device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, 
     const R piv = bcast(m[j], j);
     inv[j] = rsqrt_nr(piv);
     const R ljj = piv * inv[j];
-    const R lij = (lane == j) ? ljj : (lane > j && row ? m[j] * inv[j] : R(0));
+    const R lij = pick(lane == j, ljj, pick(lane > j && row, m[j] * inv[j], R(0)));
     m[j] = lij;
 #pragma unroll
     for (int k = j + 1; k < NV; ++k) m[k] -= lij * bcast(lij, k);
@@ -384,11 +390,31 @@ __device__ __forceinline__ void ld_op(R (&v)[10], const R* p) {
     }
   }
 }
+// a row of twelve, by 16-byte pieces
+template <class R>
+__device__ __forceinline__ void ld12(R (&v)[M], const R* p) {
+  struct alignas(16) Piece { R v[16 / sizeof(R)]; };
+  constexpr int E = 16 / int(sizeof(R));
+#pragma unroll
+  for (int i = 0; i < M; i += E) {
+    const Piece q = *reinterpret_cast<const Piece*>(p + i);
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[i + j] = q.v[j];
+  }
+}
 // its three values of an operand row of inner size 12
 template <class R>
 __device__ __forceinline__ void ld_op12(R (&v)[3], const R* p) {
+  if constexpr (sizeof(R) == 4) {
+    const mf_f4 a = *reinterpret_cast<const mf_f4*>(p);
 #pragma unroll
-  for (int i = 0; i < 3; ++i) v[i] = p[i];
+    for (int i = 0; i < 3; ++i) v[i] = a[i];
+  } else {
+    const double2 a = *reinterpret_cast<const double2*>(p);
+    v[0] = a.x;
+    v[1] = a.y;
+    v[2] = p[2];
+  }
 }
 
 // ------------------------------------------------------------------ wave Jacobians
@@ -484,15 +510,15 @@ template <int J>
 __device__ __forceinline__ double row_bcast(double v) {
   return __builtin_bit_cast(double, dpp_update_i64(0L, __builtin_bit_cast(long, v), 0x150 + J, 0xF, 0xF, true));
 }
-template <int J, class R>
-__device__ __forceinline__ void factor_col(Smem<R>& sm, double (&m)[M], bool& ok, int lane) {
+template <int J>
+__device__ __forceinline__ void factor_col(double (&m)[M], double (&invs)[M], bool& ok, int lane) {
   if constexpr (J < M) {
     const double piv = row_bcast<J>(m[J]);
     ok = ok && (piv > 0.0) && isfinite(piv);
     const double inv = rsqrt_nr(piv);
     const double ljj = piv * inv;
-    if (lane == 0) sm.Lri[J] = R(inv);
-    double lij = (lane == J) ? ljj : (lane > J && lane < M ? m[J] * inv : 0.0);
+    invs[J] = inv;
+    double lij = pick(lane == J, ljj, pick(lane > J && lane < M, m[J] * inv, 0.0));
     m[J] = lij;
     // m[k] -= l_i l_k (the wait states before a DPP read of l)
     asm("s_nop 1" : "+v"(lij));
@@ -507,7 +533,7 @@ __device__ __forceinline__ void factor_col(Smem<R>& sm, double (&m)[M], bool& ok
     if constexpr (J + 9 < M) row_fnma(m[J + 9 < M ? J + 9 : 0], lij, J + 9);
     if constexpr (J + 10 < M) row_fnma(m[J + 10 < M ? J + 10 : 0], lij, J + 10);
     if constexpr (J + 11 < M) row_fnma(m[J + 11 < M ? J + 11 : 0], lij, J + 11);
-    factor_col<J + 1, R>(sm, m, ok, lane);
+    factor_col<J + 1>(m, invs, ok, lane);
   }
 }
 template <class R>
@@ -519,53 +545,63 @@ __device__ __forceinline__ void factor_quu(Smem<R>& sm, int lane_) {
 #pragma unroll
   for (int j = 0; j < M; ++j) m[j] = row ? sm.Quu[min(ri, j)][max(ri, j)] : 0.0;
   bool ok = true;
-  factor_col<0, R>(sm, m, ok, lane);
+  double invs[M];
+  factor_col<0>(m, invs, ok, lane);
   if (row)
 #pragma unroll
     for (int j = 0; j < M; ++j) sm.Lr[ri][j] = R(m[j]);
-  if (lane == 0) sm.flag = ok ? 0 : 1;
+  if (lane == 0) {
+#pragma unroll
+    for (int j = 0; j < M; ++j) sm.Lri[j] = R(invs[j]);
+    sm.flag = ok ? 0 : 1;
+  }
 }
 
 // Column `lane` (< 38) of [K | k] from that of [Q_ux | Q_u], in registers;
-// a non-finite gain sets nonfin.
+// a non-finite gain sets nonfin.  y: the right-hand side in qc, the column in
+// kc (lanes past 37 repeat the last).
 template <class R>
-__device__ __forceinline__ void solve_gains(Smem<R>& sm, int lane_) {
-  const int lane = fresh(lane_);
-  if (lane > N) return;
-  R y[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) y[i] = lane < N ? sm.QuxT[lane][kq(i)] : sm.Qu[i];
-  R l[M][M];
-#pragma unroll
-  for (int i = 1; i < M; ++i)
-#pragma unroll
-    for (int k = 0; k < i; ++k) l[i][k] = sm.Lr[i][k];
+__device__ __forceinline__ void solve_gains(Smem<R>& sm, int lane, R (&qc)[M], R (&kc)[M]) {
+  R l[M][M], li[M];
 #pragma unroll
   for (int i = 0; i < M; ++i) {
-    R v0 = y[i], v1 = R(0);
+    ld12(l[i], sm.Lr[i]);
+    qc[i] = lane < N ? sm.QuxT[lane < N ? lane : 0][kq(i)] : sm.Qu[i];
+  }
+  ld12(li, sm.Lri);
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    R v0 = qc[i], v1 = R(0);
 #pragma unroll
     for (int k = 0; k < i; ++k) {
-      if (k & 1) v1 += l[i][k] * y[k];
-      else v0 -= l[i][k] * y[k];
+      if (k & 1) v1 += l[i][k] * kc[k];
+      else v0 -= l[i][k] * kc[k];
     }
-    y[i] = (v0 - v1) * sm.Lri[i];
+    kc[i] = (v0 - v1) * li[i];
   }
 #pragma unroll
   for (int i = M - 1; i >= 0; --i) {
-    R v0 = y[i], v1 = R(0);
+    R v0 = kc[i], v1 = R(0);
 #pragma unroll
     for (int k = i + 1; k < M; ++k) {
-      if (k & 1) v1 += l[k][i] * y[k];
-      else v0 -= l[k][i] * y[k];
+      if (k & 1) v1 += l[k][i] * kc[k];
+      else v0 -= l[k][i] * kc[k];
     }
-    y[i] = (v0 - v1) * sm.Lri[i];
+    kc[i] = (v0 - v1) * li[i];
   }
   bool fin = true;
 #pragma unroll
   for (int i = 0; i < M; ++i) {
-    fin = fin && isfinite(y[i]);
-    if (lane < N) sm.KT[lane][kq(i)] = -y[i];
-    else sm.kk[i] = -y[i];
+    fin = fin && isfinite(kc[i]);
+    kc[i] = -kc[i];
+  }
+  if (lane < N) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) sm.KT[lane][kq(i)] = kc[i];
+  }
+  if (lane == N) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) sm.kk[i] = kc[i];
   }
   if (!fin) sm.nonfin = 1;
 }
@@ -800,11 +836,12 @@ struct QW {  // workspace accessors (the lane schedule's slot-major layout)
 //   2. waves 0..2: the Q_xx tiles (w, w), (w, w + 1) and the transpose of
 //      (w + 1, w), kept in registers, and Q_ux's tile of block w; wave 3: Q_uu
 //      and its factor, the phase's longest chain;
-//   3. wave 3: the gains; waves 0..2 put the next step's derivative block,
-//      which they loaded during phase 2, into the other buffer;
+//   3. wave 3: the gains, their store and p; waves 0..2 put the next step's
+//      derivative block, which they loaded during phase 2, into the other
+//      buffer;
 //   4. waves 0..2: C = Q_xx + Q_ux^T K on their tiles and P = sym(C): a pair
 //      of tiles is symmetrised in registers, a diagonal tile through the
-//      wave's own scratch; wave 3: p and the gains' store.
+//      wave's own scratch.
 // Bound: this chain (latency of the dependent matrix instructions, of the
 // factor's twelve pivots and of LDS), of which two resident instances hide
 // each other's.  Before, with scalar operand loads under bounds checks and
@@ -831,7 +868,7 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
   __syncthreads();
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   // derivative blocks are copied by 16-byte pieces
-  struct alignas(16) Piece { R v[16 / sizeof(R)]; };
+  typedef float Piece __attribute__((ext_vector_type(4)));
   constexpr int PR = KROW * int(sizeof(R)) / 16, NP = (N + M) * PR;  // pieces per row, per block
   auto block_of = [&](int kk) { return blk + ((T - 1 - kk) % CH) * DB; };
   auto put_piece = [&](int kk, int i, const Piece& v) {
@@ -898,12 +935,12 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
     R xn = R(0), un = R(0);
     if (wid < 3) {
       if (ahead) {
+        // (all loads without a condition, so that none is waited for here)
         const Piece* src = reinterpret_cast<const Piece*>(block_of(k - 1));
 #pragma unroll
-        for (int i = 0; i < PP; ++i)
-          if (ltid + i * NS < NP) nxt[i] = src[ltid + i * NS];
-        if (ltid < N) xn = Q::xp(w, buf, k - 1, s)[ltid];
-        if (ltid < M) un = Q::up(w, buf, k - 1, s)[ltid];
+        for (int i = 0; i < PP; ++i) nxt[i] = src[min(ltid + i * NS, NP - 1)];
+        xn = Q::xp(w, buf, k - 1, s)[min(ltid, N - 1)];
+        un = Q::up(w, buf, k - 1, s)[min(ltid, M - 1)];
       }
       R ax[10], ay[10], px[10], py[10], bt[10];
       ld_op(ax, &sm.AT[cb][x0 + li][lk * KG]);
@@ -953,7 +990,28 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
     if (sm.flag) return ST_CHOL_FAIL;
     // ---- phase 3
     if (wid == 3) {
-      solve_gains(sm, lane);
+      // the gains to LDS and HBM, p = Q_x + Q_ux^T k (P's row 37 is not read
+      // before the next step); the bounded step replaces the gains first
+      R qc[M], kc[M];
+      solve_gains(sm, lane, qc, kc);
+      if constexpr (!BOX) {
+        R* dK = Q::Kp(w, k, s);
+        R kb[M];  // k in every lane (read across lanes while all are active)
+#pragma unroll
+        for (int t = 0; t < M; ++t) kb[t] = bcast(kc[t], N);
+        if (lane < N) {
+          R v = R(2) * (lane < NQ ? wq : wv) * (sm.xs[cb][lane] - sm.xnom[lane]) + sm.Qg[lane];
+#pragma unroll
+          for (int t = 0; t < M; ++t) {
+            dK[t * N + lane] = kc[t];
+            v += qc[t] * kb[t];
+          }
+          sm.P[N][kpos(lane)] = v;
+        } else if (lane == N) {
+#pragma unroll
+          for (int t = 0; t < M; ++t) Q::kp(w, k, s)[t] = kc[t];
+        }
+      }
     } else if (ahead) {
 #pragma unroll
       for (int i = 0; i < PP; ++i)
@@ -1000,7 +1058,7 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
         const R v = R(0.5) * (cd[r] + sc[li * S + i]);
         if (x0 + i < N && x0 + li < N) sm.P[x0 + i][kpos(x0 + li)] = v;
       }
-    } else {
+    } else if constexpr (BOX) {
       R* dK = Q::Kp(w, k, s);
 #pragma unroll
       for (int e = 0; e < (M * N + 63) / 64; ++e) {
