@@ -75,7 +75,7 @@ struct Smem {
   alignas(16) R Lri[M];                    // reciprocals of its diagonal
   R Qg[N + M];                             // f_x^T p, f_u^T p
   R xs[2][LD], us[2][16];                  // state and control of this and the next step
-  R Qu[16], kk[16];
+  alignas(16) R Qu[16], kk[16];
   double Quu[M][M + 1];
   // the bounded step's face factor
   double Lq[M][M + 1], Lqi[M], Li[M];
@@ -558,11 +558,10 @@ __device__ __forceinline__ void factor_quu(Smem<R>& sm, int lane_) {
 }
 
 // Column `lane` (< 38) of [K | k] from that of [Q_ux | Q_u], in registers;
-// a non-finite gain sets nonfin.  y: the right-hand side in qc, the column in
-// kc (lanes past 37 repeat the last).
+// a non-finite gain sets nonfin (lanes past 37 repeat the last column).
 template <class R>
-__device__ __forceinline__ void solve_gains(Smem<R>& sm, int lane, R (&qc)[M], R (&kc)[M]) {
-  R l[M][M], li[M];
+__device__ __forceinline__ void solve_gains(Smem<R>& sm, int lane) {
+  R l[M][M], li[M], qc[M], kc[M];
 #pragma unroll
   for (int i = 0; i < M; ++i) {
     ld12(l[i], sm.Lr[i]);
@@ -836,12 +835,11 @@ struct QW {  // workspace accessors (the lane schedule's slot-major layout)
 //   2. waves 0..2: the Q_xx tiles (w, w), (w, w + 1) and the transpose of
 //      (w + 1, w), kept in registers, and Q_ux's tile of block w; wave 3: Q_uu
 //      and its factor, the phase's longest chain;
-//   3. wave 3: the gains, their store and p; waves 0..2 put the next step's
-//      derivative block, which they loaded during phase 2, into the other
-//      buffer;
+//   3. wave 3: the gains; waves 0..2 put the next step's derivative block,
+//      which they loaded during phase 2, into the other buffer;
 //   4. waves 0..2: C = Q_xx + Q_ux^T K on their tiles and P = sym(C): a pair
 //      of tiles is symmetrised in registers, a diagonal tile through the
-//      wave's own scratch.
+//      wave's own scratch; wave 3: the gains' store and p.
 // Bound: this chain (latency of the dependent matrix instructions, of the
 // factor's twelve pivots and of LDS), of which two resident instances hide
 // each other's.  Before, with scalar operand loads under bounds checks and
@@ -990,28 +988,7 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
     if (sm.flag) return ST_CHOL_FAIL;
     // ---- phase 3
     if (wid == 3) {
-      // the gains to LDS and HBM, p = Q_x + Q_ux^T k (P's row 37 is not read
-      // before the next step); the bounded step replaces the gains first
-      R qc[M], kc[M];
-      solve_gains(sm, lane, qc, kc);
-      if constexpr (!BOX) {
-        R* dK = Q::Kp(w, k, s);
-        R kb[M];  // k in every lane (read across lanes while all are active)
-#pragma unroll
-        for (int t = 0; t < M; ++t) kb[t] = bcast(kc[t], N);
-        if (lane < N) {
-          R v = R(2) * (lane < NQ ? wq : wv) * (sm.xs[cb][lane] - sm.xnom[lane]) + sm.Qg[lane];
-#pragma unroll
-          for (int t = 0; t < M; ++t) {
-            dK[t * N + lane] = kc[t];
-            v += qc[t] * kb[t];
-          }
-          sm.P[N][kpos(lane)] = v;
-        } else if (lane == N) {
-#pragma unroll
-          for (int t = 0; t < M; ++t) Q::kp(w, k, s)[t] = kc[t];
-        }
-      }
+      solve_gains(sm, lane);
     } else if (ahead) {
 #pragma unroll
       for (int i = 0; i < PP; ++i)
@@ -1058,20 +1035,32 @@ __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restri
         const R v = R(0.5) * (cd[r] + sc[li * S + i]);
         if (x0 + i < N && x0 + li < N) sm.P[x0 + i][kpos(x0 + li)] = v;
       }
-    } else if constexpr (BOX) {
+    } else {
       R* dK = Q::Kp(w, k, s);
+      R kb[M], kc[M], qc[M];
+      ld12(kb, sm.kk);
+      const int row = lane < N ? lane : 0;
 #pragma unroll
-      for (int e = 0; e < (M * N + 63) / 64; ++e) {
-        const int i = e * 64 + lane, t = i / N;
-        if (i < M * N) dK[i] = sm.KT[i - t * N][kq(t)];
+      for (int g = 0; g < 4; ++g) {
+        R a[3], b[3];
+        ld_op12(a, &sm.KT[row][4 * g]);
+        ld_op12(b, &sm.QuxT[row][4 * g]);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+          kc[g + 4 * t] = a[t];
+          qc[g + 4 * t] = b[t];
+        }
       }
-      if (lane < M) Q::kp(w, k, s)[lane] = sm.kk[lane];
       if (lane < N) {
         R v = R(2) * (lane < NQ ? wq : wv) * (sm.xs[cb][lane] - sm.xnom[lane]) + sm.Qg[lane];
 #pragma unroll
-        for (int t = 0; t < M; ++t) v += sm.QuxT[lane][kq(t)] * sm.kk[t];
+        for (int t = 0; t < M; ++t) {
+          dK[t * N + lane] = kc[t];
+          v += qc[t] * kb[t];
+        }
         sm.P[N][kpos(lane)] = v;
       }
+      if (lane < M) Q::kp(w, k, s)[lane] = sm.kk[lane];
     }
     __syncthreads();
   }
