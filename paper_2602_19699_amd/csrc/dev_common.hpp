@@ -320,6 +320,49 @@ __device__ __forceinline__ bool box_qp(const double (&H)[M][M], const double (&g
       up |= 1u << i;
     }
   }
+  if constexpr (M == 2) {
+    // Two controls: the usual courses of the loop below (one held component
+    // whose face minimiser lies in the box, or meets a bound; both held; no
+    // multiplier negative) in line, with the loop's own arithmetic and without
+    // its divisions: a step fraction t = (bound - d) / (y - d) is below 1
+    // exactly when the numerator is the smaller.  The wave takes the loop only
+    // where a multiplier asks for a release.  Point mass, 1000 instances at
+    // the bound, horizons 20..200: 2.24 -> 1.93 ms per solve (same box).
+    const int f = W == 1u ? 1 : 0;  // the free component, if one is
+    const bool one = W != ALL;
+    const double Hf = f ? H[1][1] : H[0][0], lof = f ? lo[1] : lo[0], hif = f ? hi[1] : hi[0];
+    const double df = f ? d[1] : d[0], dh = f ? d[0] : d[1];
+    double inv = __builtin_amdgcn_rsq(Hf);
+#pragma unroll
+    for (int it = 0; it < NR; ++it) inv = inv * (1.5 - 0.5 * Hf * inv * inv);
+    if (one && !(Hf > 0.0 && isfinite(Hf))) return false;
+    const double v = (f ? g[1] : g[0]) + H[0][1] * dh;
+    const double y = -v * inv * inv;
+    const double p = y - df;
+    const bool low = p < 0.0 && lof - df > p, high = p > 0.0 && hif - df < p;
+    const double dn = low ? lof : (high ? hif : y);
+    const unsigned Wn = one && (low || high) ? ALL : W;
+    const unsigned un = one ? (high ? up | (1u << f) : (low ? up & ~(1u << f) : up)) : up;
+    const double e0 = one && f == 0 ? dn : d[0], e1 = one && f == 1 ? dn : d[1];
+    double g0 = g[0], g1 = g[1];
+    g0 += H[0][0] * e0;
+    g0 += H[0][1] * e1;
+    g1 += H[0][1] * e0;
+    g1 += H[1][1] * e1;
+    const bool neg = ((Wn & 1u) && ((un & 1u) ? -g0 : g0) < 0.0) || ((Wn & 2u) && ((un & 2u) ? -g1 : g1) < 0.0);
+    if (!neg) {
+      d[0] = e0;
+      d[1] = e1;
+      const bool face = Wn != ALL;
+      lf[0][0] = face && f == 0 ? Hf * inv : 1.0;
+      lf[1][1] = face && f == 1 ? Hf * inv : 1.0;
+      lf[1][0] = 0.0;
+      invf[0] = face && f == 0 ? inv : 1.0;
+      invf[1] = face && f == 1 ? inv : 1.0;
+      W = Wn;
+      return true;
+    }
+  }
   auto h = [&](int i, int j) { return i <= j ? H[i][j] : H[j][i]; };
   auto factor_face = [&]() -> bool {
     double hm[M][M];
@@ -332,6 +375,7 @@ __device__ __forceinline__ bool box_qp(const double (&H)[M][M], const double (&g
   };
   constexpr int cap = 4 * M + 4;
   bool at_min = false;
+  unsigned factored = ALL;  // the working set whose face lf/invf hold (ALL: none)
   for (int it = 0; it < cap; ++it) {
     if (!at_min) {
       if (W == ALL) {
@@ -339,6 +383,7 @@ __device__ __forceinline__ bool box_qp(const double (&H)[M][M], const double (&g
         continue;
       }
       if (!factor_face()) return false;
+      factored = W;
       double y[M];
 #pragma unroll
       for (int i = 0; i < M; ++i) {
@@ -406,7 +451,9 @@ __device__ __forceinline__ bool box_qp(const double (&H)[M][M], const double (&g
       at_min = false;
     }
   }
-  // the factor of the final face
+  // the factor of the final face (usually the one factored last, which moved
+  // the step to the face's minimiser: factoring it again would give the same)
+  if (W == factored && W != ALL) return true;
   if (W == 0) return chol_fp64<M, NR>(H, lf, invf);
   if (W == ALL) {
 #pragma unroll

@@ -89,3 +89,20 @@ def test_quadruped_chunk_edges(ctx, prec, form):
     for wg in (1, 2):  # either schedule
         _equal(g, gpu_solve(ctx, I.SYS_QUAD_SYNTH, p, x0, 37, T=T, precision=prec, wg_per_cu=wg, **o),
                [k for k in FIELDS if g[k] is not None], f"wg_per_cu={wg}")
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("u_max", [0.5, 3.0, 10.0, 30.0])
+def test_two_control_bound_from_rarely_to_always_active(ctx, prec, u_max):
+    # the in-line courses of the two-control box QP and its loop (released
+    # bounds): against the oracle, and every group width alike
+    p, x0 = I.point_mass_params(0), I.point_mass_x0(200, 12)
+    T = I.horizons(200, 1, 60, 13)
+    o = dict(u_max=u_max, max_iter=25, stop_mode=1, rtol=1e-10 if prec == 0 else 1e-7)
+    g = gpu_solve(ctx, PM, p, x0, 60, T=T, precision=prec, **o)
+    r = orc.solve_batch(PM, p, x0, 60, T=T, opts=oracle_opts(**{**o, "rtol": 1e-10}))
+    assert np.all(rel(g["J"], r.J) <= (1e-9 if prec == 0 else 1e-4))
+    assert np.all(np.abs(g["U"]) <= u_max)
+    for gl in (1, 4):
+        _equal(g, gpu_solve(ctx, PM, p, x0, 60, T=T, precision=prec, group_lanes=gl, **o),
+               ["X", "U", "J", "iters", "status", "Vbar", "Vx"], f"{gl}")
