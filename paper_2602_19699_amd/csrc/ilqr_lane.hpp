@@ -1384,6 +1384,11 @@ struct Lane {
   // Step record of the line-search stream: x_k, u_k, K_k, k_k, padded to 16 B.
   static constexpr int SW = N + M + M * N + M;
   static constexpr int SWP = (SW + 3) & ~3;
+  // rollout steps unrolled: with four the records of the later ones are read
+  // while the first runs (point mass, mixed, B = 64: 348 -> 339 us per solve, B =
+  // 16384: 576 -> 566); FP64 and the arm are slower with four (the arm's FP64
+  // solve 25.7 -> 27.4 ms)
+  static constexpr int kTrialUnroll = sizeof(R) == 4 && Sys::kAxisPairs ? 4 : 2;
   // steps each lane loads per chunk
   static constexpr int PT = SWP * int(sizeof(R)) <= 64 ? 2 : 1;
 
@@ -1464,8 +1469,9 @@ struct Lane {
         // the stop test is taken at the end of the chunk, so that no step
         // waits on the branch of the one before (steps past the first
         // failing one change neither the decision nor the counts)
-        bool failed = false;
-#pragma unroll 2
+        bool under = true;  // every step so far kept the cost below J
+        int nunder = 0;
+#pragma unroll kTrialUnroll
         for (int q = 0; q < cn; ++q) {
           const R* v = cur + q * SWP;
           const int k = kc + q;
@@ -1490,12 +1496,15 @@ struct Lane {
             st(xp(w, nb, k + 1, s), xh);
           }
           if constexpr (Sys::kNonNegCost && !REPLAY) {
-            const bool f = !(Jh < Jcur);
-            steps = (f && !failed) ? k + 1 : steps;
-            failed = failed || f;
+            under = under && Jh < Jcur;
+            nunder += under ? 1 : 0;
           }
         }
-        if (failed) live = false;
+        if constexpr (Sys::kNonNegCost && !REPLAY)
+          if (!under) {
+            steps = kc + nunder + 1;
+            live = false;
+          }
       }
       const unsigned long long any = (__ballot(live) >> gbase) & gmask;
       if (!any || !more) break;
@@ -1736,7 +1745,7 @@ __global__ void __launch_bounds__(64) lane_iterate(const double* __restrict__ pr
           int steps = 0;
           double alpha = 1.0;
           for (int q = 0; q < j; ++q) alpha *= sp.beta;
-          const double Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, wb, R(alpha), J, run, run, steps, stage,
+          const double Jh = LN::template trial<GL, BOX>(mdl, w, s, T, buf, wb, R(alpha), J, run, true, steps, stage,
                                                         r, gbase, R(sp.umax));
           ++npass;
           // every lane writes what it rolled out; the lanes of a group read the
