@@ -1486,9 +1486,9 @@ struct Lane {
             if constexpr (BOX) u = clamp_nan(u, umax);
             uh[i] = u;
           }
-          if constexpr (!REPLAY) Jh += double(mdl.cost(xh, uh));
           R xn[N];
-          mdl.dyn(xh, uh, xn);
+          if constexpr (REPLAY) mdl.dyn(xh, uh, xn);
+          else Jh += double(mdl.cost_dyn(xh, uh, xn));
 #pragma unroll
           for (int i = 0; i < N; ++i) xh[i] = xn[i];
           if (write) {
