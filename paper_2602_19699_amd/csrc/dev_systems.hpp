@@ -324,8 +324,6 @@ struct Arm3 {
       }
     }
 
-    // constants of the Riccati step: dt, the clipped control Hessian (2 w_u)
-    // and the clipped velocity Hessian (zero)
     // the running cost and the step together, from one evaluation of the
     // angles: apart, the sine and cosine of each were taken twice in FP64 (the
     // library code has branches, past which the compiler keeps both); 500 arm
@@ -337,6 +335,8 @@ struct Arm3 {
       return cost(t, u);
     }
 
+    // constants of the Riccati step: dt, the clipped control Hessian (2 w_u)
+    // and the clipped velocity Hessian (zero)
     CBIC_HD __forceinline__ R step_dt() const { return R(p[0]); }
     CBIC_HD __forceinline__ R ctrl_hess(R eps) const { return dmax(R(2) * R(p[10]), eps); }
     CBIC_HD __forceinline__ R vel_hess(R eps) const { return dmax(R(0), eps); }

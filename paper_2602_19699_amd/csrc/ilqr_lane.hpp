@@ -535,8 +535,9 @@ struct Lane {
   // wave per SIMD, so a step costs what one wave takes to issue it.  The split
   // over a lane pair issues about 690 instructions per step in FP32, this one
   // 240 (FP64 275): 4096 arm instances of horizons 50..200, mixed, 20.3 ->
-  // 13.7 ms per solve; 500 in FP64 with 50 iterations 33.4 -> 25.7 ms.  Narrower
-  // groups do not hold nine columns and keep the lane pair.
+  // 13.7 ms per solve; 500 in FP64 with 50 iterations 33.4 -> 25.7 ms (20.0 now,
+  // with the arm's angles evaluated once a step).  Narrower groups do not hold
+  // nine columns and keep the lane pair.
   template <int GL>
   static constexpr bool kRow = GL == 16 && Sys::kSemiImplicit && N == 6 && M == 3;
   // stride of a staged derivative block: whole 16-byte pieces for the row

@@ -112,8 +112,8 @@ __device__ __forceinline__ void wave_sync() {
 // formed where it is used.  Derived from the lane number itself, they are
 // invariant over the whole solve, and the compiler keeps hundreds of them
 // through it, in scratch memory (145 registers of the mixed kernel for two
-// instances per CU, 173 of the FP64 one; with them 11.2 instead of 8.8 ms, and
-// 11.1 instead of 9.3).
+// instances per CU, 173 of the FP64 one): a quarter more time for 1024 mixed
+// instances, a fifth more for 100 in FP64.
 __device__ __forceinline__ int fresh(int v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -250,7 +250,7 @@ __device__ __forceinline__ R backward_step(R y, R l, R inv, int j, int lane) {
 // is loaded in wide pieces ahead of the chains.  A step of a line-search trial
 // takes 9.3 thousand cycles alone on its SIMD (17.9 with a branch per entry,
 // single loads inside the chains and shuffle sums); solve of 1024 mixed
-// instances 8.8 -> 6.5 ms, of 100 in FP64 9.3 -> 7.2 ms.
+// instances 2.3 ms shorter, of 100 in FP64 2.1 ms (of 8.8 and 9.3 ms).
 template <class R, class S>
 __device__ __forceinline__ void wave_dyn(const S& sm, WaveScratch<R>& ws, R dt, int lane_) {
   const int lane = fresh(lane_);
@@ -844,8 +844,9 @@ struct QW {  // workspace accessors (the lane schedule's slot-major layout)
 // factor's twelve pivots and of LDS), of which two resident instances hide
 // each other's.  Before, with scalar operand loads under bounds checks and
 // Q_xx, C and its symmetrised form through LDS, a step took six barriers and
-// 1024 mixed instances 13.0 ms per solve, 100 in FP64 13.9; now 8.8 and 9.3 (a
-// step's phases take 2.2, 7.1, 2.9 and 2.7 thousand cycles).
+// 1024 mixed instances 13.0 ms per solve, 100 in FP64 13.9; now 5.9 and 5.9,
+// with wave_dyn's share (a step's phases take 2.4, 5.6, 2.6 and 2.7 thousand
+// cycles with two instances per CU).
 template <class R, bool BOX>
 __device__ __forceinline__ uint32_t backward(Smem<R>& sm, const double* __restrict__ prm, const LaneState<R>& w, int s, int T,
                              int buf, R eps, int tid, R* __restrict__ blk, double mu, double umax) {

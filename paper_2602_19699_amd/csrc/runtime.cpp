@@ -78,14 +78,16 @@ int cu_count(int device) {
 // SIMDs once (65536 lanes), for every instance.  The other work of a group,
 // the derivative blocks and the arm's columns, shares out over more lanes than
 // that, so the groups are wider: 16 lanes up to wide_lanes (two waves per
-// SIMD, four for the arm in FP32), 8 beyond.  Measured (solve, us, 4 / 8 / 16
-// lanes): point mass, mixed, tol 1e-4: B 8192 662 / 509 / 455, B 16384 667 /
-// 538 / 732, B 32768 941 / 916 / 1290 (2 lanes 1293); FP64: B 8192 1310 / 997 /
-// 943, B 16384 1373 / 1140 / 1510; arm (8 / 16 lanes), mixed: B 8192 12035 /
-// 8539, B 16384 13778 / 13056, B 32768 21678 / 22801; FP64: B 8192 20740 /
-// 18639, B 12000 23553 / 26431.  The linear-quadratic kernels have nothing to
-// share and are slower in wider groups (6 states, FP64, B 16384: 4 / 8 lanes
-// 2176 / 3090).
+// SIMD, four for the arm in FP32), 8 beyond.  Measured with rounds as wide as
+// the group (solve, us, 4 / 8 / 16 lanes; in brackets what this function
+// gives): point mass, mixed, tol 1e-4: B 8192 654 / 496 / 454 (491), B 16384
+// 634 / 530 / 717 (582), B 32768 939 / 905 / 1259 (1205; 2 lanes, the same
+// rounds, 1229); FP64: B 8192 1264 / 997 / 935 (934), B 16384 1340 / 1126 / 1513
+// (1267); arm (8 / 16 lanes), mixed: B 8192 11918 / 8545 (7804), B 16384 13810 /
+// 13104 (11400), B 32768 21735 / 22296 (23435); FP64: B 8192 17968 / 14932
+// (13468), B 12000 20120 / 21328 (24310).  The linear-quadratic kernels have
+// nothing to share and are slower in wider groups (6 states, FP64, B 16384: 4 /
+// 8 lanes 2176 / 3090).
 int default_group(const Launcher* L, int B, int precision, int device) {
   if (L->schedule == CBIC_SCHED_GROUP) return (precision == CBIC_FP64 || B <= cu_count(device)) ? 1 : 2;
   int trials = 1;
