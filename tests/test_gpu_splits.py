@@ -106,3 +106,25 @@ def test_two_control_bound_from_rarely_to_always_active(ctx, prec, u_max):
     for gl in (1, 4):
         _equal(g, gpu_solve(ctx, PM, p, x0, 60, T=T, precision=prec, group_lanes=gl, **o),
                ["X", "U", "J", "iters", "status", "Vbar", "Vx"], f"{gl}")
+
+
+@pytest.mark.parametrize("lanes", [1, 16])
+def test_arm_angles_past_the_short_range(ctx, lanes):
+    # angles around 2^30, where the FP64 sine and cosine change course, and far
+    # past it; one angle at a time, so that the absolute angles are exact sums.
+    # A step's velocities are dt M^-1 (tau - b): errors of a few ulp, grown by
+    # the mass matrix's condition (below 1e3)
+    p = I.planar3_params(0)
+    a = np.array([2.0**30 - 0.5, 2.0**30, 2.0**30 + 0.5, -(2.0**30) - 0.5, 1e12, 3e15])
+    x0 = np.zeros((3 * len(a), 6))
+    for j in range(3):
+        x0[j * len(a):(j + 1) * len(a), j] = a
+    x0[:, 3:] = [0.3, -0.4, 0.5]
+    U0 = np.tile([1.0, -2.0, 0.5], (len(x0), 2, 1))
+    got = gpu_solve(ctx, P3, p, x0, 2, U0=U0, group_lanes=lanes, precision=0, max_iter=0)
+    want = np.stack([orc.dyn(P3, p, x0[b], U0[b, 0]) for b in range(len(x0))])
+    v = want[:, 3:]
+    assert np.max(np.abs(got["X"][:, 1, 3:] - v)) <= 1e3 * 8 * np.finfo(float).eps * np.max(np.abs(v))
+    one = gpu_solve(ctx, P3, p, x0, 2, U0=U0, group_lanes=1, precision=0, max_iter=2, trace=True)
+    _equal(one, gpu_solve(ctx, P3, p, x0, 2, U0=U0, group_lanes=lanes, precision=0, max_iter=2, trace=True),
+           [k for k in FIELDS if k != "work"])
