@@ -503,8 +503,49 @@ __device__ __forceinline__ void wave_jac(const Smem<R>& sm, const WaveScratch<R>
 // reaches the other lanes by row broadcasts, which the subtraction reads as an
 // operand) to its factor in R (the mixed form's gain solves run in FP32 on the
 // FP64 factor rounded to FP32, as in the lane kernels).
-__device__ __forceinline__ void row_fnma(double& m, double l, int k) {
-  asm("v_fmac_f64_dpp %0, -%1, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(m) : "v"(l), "n"(k));
+//
+// row_fnma_past<J>: m[k] -= l l_k (l_k: lane k's l) for the columns k past J,
+// in one statement with the wait states that a DPP read of l needs after the
+// write of it: in statements of their own the compiler may place a copy or a
+// reload of l between the two.
+#define CBIC_FNMA(K) "v_fmac_f64_dpp %[m" #K "], -%[l], %[l] row_newbcast:" #K " row_mask:0xf bank_mask:0xf\n\t"
+#define CBIC_FNMA_IO(K) [m##K] "+&v"(m[K])
+#define CBIC_FNMA_11 CBIC_FNMA(11)
+#define CBIC_FNMA_10 CBIC_FNMA(10) CBIC_FNMA_11
+#define CBIC_FNMA_9 CBIC_FNMA(9) CBIC_FNMA_10
+#define CBIC_FNMA_8 CBIC_FNMA(8) CBIC_FNMA_9
+#define CBIC_FNMA_7 CBIC_FNMA(7) CBIC_FNMA_8
+#define CBIC_FNMA_6 CBIC_FNMA(6) CBIC_FNMA_7
+#define CBIC_FNMA_5 CBIC_FNMA(5) CBIC_FNMA_6
+#define CBIC_FNMA_4 CBIC_FNMA(4) CBIC_FNMA_5
+#define CBIC_FNMA_3 CBIC_FNMA(3) CBIC_FNMA_4
+#define CBIC_FNMA_2 CBIC_FNMA(2) CBIC_FNMA_3
+#define CBIC_FNMA_1 CBIC_FNMA(1) CBIC_FNMA_2
+#define CBIC_FNMA_IO_11 CBIC_FNMA_IO(11)
+#define CBIC_FNMA_IO_10 CBIC_FNMA_IO(10), CBIC_FNMA_IO_11
+#define CBIC_FNMA_IO_9 CBIC_FNMA_IO(9), CBIC_FNMA_IO_10
+#define CBIC_FNMA_IO_8 CBIC_FNMA_IO(8), CBIC_FNMA_IO_9
+#define CBIC_FNMA_IO_7 CBIC_FNMA_IO(7), CBIC_FNMA_IO_8
+#define CBIC_FNMA_IO_6 CBIC_FNMA_IO(6), CBIC_FNMA_IO_7
+#define CBIC_FNMA_IO_5 CBIC_FNMA_IO(5), CBIC_FNMA_IO_6
+#define CBIC_FNMA_IO_4 CBIC_FNMA_IO(4), CBIC_FNMA_IO_5
+#define CBIC_FNMA_IO_3 CBIC_FNMA_IO(3), CBIC_FNMA_IO_4
+#define CBIC_FNMA_IO_2 CBIC_FNMA_IO(2), CBIC_FNMA_IO_3
+#define CBIC_FNMA_IO_1 CBIC_FNMA_IO(1), CBIC_FNMA_IO_2
+template <int J>
+__device__ __forceinline__ void row_fnma_past(double (&m)[M], double l) {
+  static_assert(M == 12, "one statement per column of a 12-wide factor");
+  if constexpr (J == 0) asm("s_nop 1\n\t" CBIC_FNMA_1 : CBIC_FNMA_IO_1 : [l] "v"(l));
+  if constexpr (J == 1) asm("s_nop 1\n\t" CBIC_FNMA_2 : CBIC_FNMA_IO_2 : [l] "v"(l));
+  if constexpr (J == 2) asm("s_nop 1\n\t" CBIC_FNMA_3 : CBIC_FNMA_IO_3 : [l] "v"(l));
+  if constexpr (J == 3) asm("s_nop 1\n\t" CBIC_FNMA_4 : CBIC_FNMA_IO_4 : [l] "v"(l));
+  if constexpr (J == 4) asm("s_nop 1\n\t" CBIC_FNMA_5 : CBIC_FNMA_IO_5 : [l] "v"(l));
+  if constexpr (J == 5) asm("s_nop 1\n\t" CBIC_FNMA_6 : CBIC_FNMA_IO_6 : [l] "v"(l));
+  if constexpr (J == 6) asm("s_nop 1\n\t" CBIC_FNMA_7 : CBIC_FNMA_IO_7 : [l] "v"(l));
+  if constexpr (J == 7) asm("s_nop 1\n\t" CBIC_FNMA_8 : CBIC_FNMA_IO_8 : [l] "v"(l));
+  if constexpr (J == 8) asm("s_nop 1\n\t" CBIC_FNMA_9 : CBIC_FNMA_IO_9 : [l] "v"(l));
+  if constexpr (J == 9) asm("s_nop 1\n\t" CBIC_FNMA_10 : CBIC_FNMA_IO_10 : [l] "v"(l));
+  if constexpr (J == 10) asm("s_nop 1\n\t" CBIC_FNMA_11 : CBIC_FNMA_IO_11 : [l] "v"(l));
 }
 template <int J>
 __device__ __forceinline__ double row_bcast(double v) {
@@ -518,21 +559,9 @@ __device__ __forceinline__ void factor_col(double (&m)[M], double (&invs)[M], bo
     const double inv = rsqrt_nr(piv);
     const double ljj = piv * inv;
     invs[J] = inv;
-    double lij = pick(lane == J, ljj, pick(lane > J && lane < M, m[J] * inv, 0.0));
+    const double lij = pick(lane == J, ljj, pick(lane > J && lane < M, m[J] * inv, 0.0));
     m[J] = lij;
-    // m[k] -= l_i l_k (the wait states before a DPP read of l)
-    asm("s_nop 1" : "+v"(lij));
-    if constexpr (J + 1 < M) row_fnma(m[J + 1 < M ? J + 1 : 0], lij, J + 1);
-    if constexpr (J + 2 < M) row_fnma(m[J + 2 < M ? J + 2 : 0], lij, J + 2);
-    if constexpr (J + 3 < M) row_fnma(m[J + 3 < M ? J + 3 : 0], lij, J + 3);
-    if constexpr (J + 4 < M) row_fnma(m[J + 4 < M ? J + 4 : 0], lij, J + 4);
-    if constexpr (J + 5 < M) row_fnma(m[J + 5 < M ? J + 5 : 0], lij, J + 5);
-    if constexpr (J + 6 < M) row_fnma(m[J + 6 < M ? J + 6 : 0], lij, J + 6);
-    if constexpr (J + 7 < M) row_fnma(m[J + 7 < M ? J + 7 : 0], lij, J + 7);
-    if constexpr (J + 8 < M) row_fnma(m[J + 8 < M ? J + 8 : 0], lij, J + 8);
-    if constexpr (J + 9 < M) row_fnma(m[J + 9 < M ? J + 9 : 0], lij, J + 9);
-    if constexpr (J + 10 < M) row_fnma(m[J + 10 < M ? J + 10 : 0], lij, J + 10);
-    if constexpr (J + 11 < M) row_fnma(m[J + 11 < M ? J + 11 : 0], lij, J + 11);
+    row_fnma_past<J>(m, lij);
     factor_col<J + 1>(m, invs, ok, lane);
   }
 }
