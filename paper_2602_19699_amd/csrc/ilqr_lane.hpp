@@ -568,7 +568,8 @@ struct Lane {
 
   // acc[i] = fma(s_c of lane i, m_c, acc[i]) for c = 0, 1, 2 in turn and
   // i = 0..5 (the s_nop covers the two wait states between a vector write of
-  // s_c and its DPP read)
+  // s_c and its DPP read; the accumulators are written before the last input is
+  // read, so they share no register with one: "+&v")
 #define CBIC_ROW6(OP, S, Q)                                                     \
   OP " %0, " S ", " Q " row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"          \
   OP " %1, " S ", " Q " row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"          \
@@ -580,12 +581,12 @@ struct Lane {
     if constexpr (sizeof(R) == 4)
       asm("s_nop 1\n\t" CBIC_ROW6("v_fmac_f32_dpp", "%6", "%9") CBIC_ROW6("v_fmac_f32_dpp", "%7", "%10")
               CBIC_ROW6("v_fmac_f32_dpp", "%8", "%11")
-          : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5])
+          : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5])
           : "v"(s0), "v"(s1), "v"(s2), "v"(m0), "v"(m1), "v"(m2));
     else
       asm("s_nop 1\n\t" CBIC_ROW6("v_fmac_f64_dpp", "%6", "%9") CBIC_ROW6("v_fmac_f64_dpp", "%7", "%10")
               CBIC_ROW6("v_fmac_f64_dpp", "%8", "%11")
-          : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5])
+          : "+&v"(a[0]), "+&v"(a[1]), "+&v"(a[2]), "+&v"(a[3]), "+&v"(a[4]), "+&v"(a[5])
           : "v"(s0), "v"(s1), "v"(s2), "v"(m0), "v"(m1), "v"(m2));
   }
 #undef CBIC_ROW6
@@ -595,12 +596,12 @@ struct Lane {
     if constexpr (sizeof(R) == 4)
       asm("s_nop 1\n\t" CBIC_ROW1("v_fmac_f32_dpp", "0", "%2") CBIC_ROW1("v_fmac_f32_dpp", "1", "%3")
               CBIC_ROW1("v_fmac_f32_dpp", "2", "%4")
-          : "+v"(a)
+          : "+&v"(a)
           : "v"(s), "v"(m0), "v"(m1), "v"(m2));
     else
       asm("s_nop 1\n\t" CBIC_ROW1("v_fmac_f64_dpp", "0", "%2") CBIC_ROW1("v_fmac_f64_dpp", "1", "%3")
               CBIC_ROW1("v_fmac_f64_dpp", "2", "%4")
-          : "+v"(a)
+          : "+&v"(a)
           : "v"(s), "v"(m0), "v"(m1), "v"(m2));
 #undef CBIC_ROW1
   }

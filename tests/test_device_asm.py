@@ -57,3 +57,18 @@ def test_dpp_reads_wait_in_their_own_statement(name, line, text):
     # it, which the compiler does not insert inside a statement; the wait of
     # another statement does not cover a copy or reload placed between them
     assert re.match(r'\(\s*"s_nop 1\\n', text), f"{name}:{line} reads by DPP without waiting first"
+
+
+def _outputs(text):
+    """The output part of a statement: between its first and second colon outside literals."""
+    bare = re.sub(r'"((?:[^"\\]|\\.)*)"', lambda m: '"' + m.group(1).replace(":", ";") + '"', text)
+    return bare.split(":")[1]
+
+
+@pytest.mark.parametrize("name,line,text", DPP, ids=[f"{n}:{i}" for i, (n, _, _) in enumerate(DPP)])
+def test_accumulators_share_no_register_with_an_input(name, line, text):
+    # these statements write accumulators before they have read the last input:
+    # without the early-clobber mark an input whose value the compiler knows to
+    # equal an accumulator's could be given the accumulator's register
+    outs = re.findall(r'"([^"]*)"\s*\(', _outputs(text))
+    assert outs and all(o == "+&v" for o in outs), f"{name}:{line} {outs}"
