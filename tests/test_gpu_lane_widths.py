@@ -1,0 +1,42 @@
+"""Line-search rounds that do not fill a group: last rounds with fewer trials
+than lanes, and groups wider than their rounds, in every form of a solve."""
+import numpy as np
+import pytest
+
+from paper_2602_19699_amd import inputs as I
+
+from gpu_helpers import gpu_solve
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("X", "U", "J", "iters", "status", "Vbar", "Vx", "xK", "cost_trace", "work", "jtrace")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    from paper_2602_19699_amd import cbic
+    assert torch.cuda.is_available()
+    c = cbic.Context(0)
+    yield c
+    c.close()
+
+
+def _equal(a, b, fields=FIELDS, what=""):
+    for k in fields:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=f"{what} field {k}")
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("n,m", [(2, 1), (4, 2), (6, 3)])
+@pytest.mark.parametrize("trials", [1, 3, 11, 16])
+def test_lq_trial_budget_of_any_size(ctx, n, m, trials, prec):
+    # a linear-quadratic solve is at its optimum after one step: the second
+    # iteration's line search finds no decrease and runs through its budget,
+    # the last round with fewer trials than lanes
+    p, x0 = I.lq_random(n, m, 0), I.lq_x0(37, n)
+    o = dict(T=I.horizons(37, 1, 40, 6), precision=prec, max_iter=4, ls_max_trials=trials, trace=True)
+    ref = gpu_solve(ctx, I.SYS_LQ, p, x0, 40, group_lanes=1, **o)
+    assert np.all(ref["work"][:, 0] >= 2)
+    for g in (2, 4, 8, 16):
+        _equal(ref, gpu_solve(ctx, I.SYS_LQ, p, x0, 40, group_lanes=g, **o), [k for k in FIELDS if k != "work"], f"{g}")
