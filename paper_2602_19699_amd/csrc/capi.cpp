@@ -239,7 +239,7 @@ cbic_status enqueue_solve(cbic_context* ctx, const cbic_system* sys, const doubl
   int group = requested_group(L, opts);
   if (group <= 0) {
     auto it = ctx->tuned.find(tune_key(sys, B, Tmax, opts));
-    group = it != ctx->tuned.end() ? it->second : default_group(L, B, opts->precision, ctx->device);
+    group = it != ctx->tuned.end() ? it->second : default_group(L, B, opts, d_T != nullptr, ctx->device);
   }
   if (opts->max_iter > 0) {
     const int G = opts->iters_per_launch > 0 ? std::min(opts->iters_per_launch, opts->max_iter) : opts->max_iter;

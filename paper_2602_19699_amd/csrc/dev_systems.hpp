@@ -34,7 +34,7 @@ struct PointMass {
   // f_x and f_u do not depend on (x, u)
   static constexpr bool kConstJac = true;
   static constexpr bool kSemiImplicit = false;  // (constant Jacobians: nothing to factor)
-  // lanes of a batch up to which its groups widen to 16 lanes (default_group)
+  // lanes of a batch up to which its groups may widen to 16 lanes (default_group)
   template <class R> static constexpr int kWideLanes() { return 131072; }
   // structural nonzeros of f_x and f_u (A = [[I, dt I], [0, I]], B = [[dt^2 I], [dt I]])
   __host__ __device__ static constexpr bool a_nz(int i, int j) { return i == j || j == i + 2; }
@@ -229,7 +229,7 @@ struct Arm3 {
   // q+ = q + dt qd+: the backward sweep takes the Jacobians in factored form
   static constexpr bool kSemiImplicit = true;
   // the 16-lane sweep issues a third of the instructions of a narrower one; in
-  // FP64 two waves per SIMD no longer fit its registers
+  // FP64 no more than two of its waves share a SIMD (registers)
   template <class R> static constexpr int kWideLanes() { return sizeof(R) == 4 ? 262144 : 131072; }
   __host__ __device__ static constexpr bool a_nz(int, int) { return true; }
   __host__ __device__ static constexpr bool b_nz(int, int) { return true; }

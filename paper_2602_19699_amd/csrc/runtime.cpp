@@ -8,6 +8,7 @@
 #include <cstring>
 #include <algorithm>
 #include <atomic>
+#include <climits>
 
 namespace cbic {
 
@@ -75,26 +76,65 @@ int cu_count(int device) {
 }
 
 // Lane schedule: a line-search round tries as many steps as fill the chip's
-// SIMDs once (65536 lanes), for every instance.  The other work of a group,
-// the derivative blocks and the arm's columns, shares out over more lanes than
-// that, so the groups are wider: 16 lanes up to wide_lanes (two waves per
-// SIMD, four for the arm in FP32), 8 beyond.  Measured with rounds as wide as
-// the group (solve, us, 4 / 8 / 16 lanes; in brackets what this function
-// gives): point mass, mixed, tol 1e-4: B 8192 654 / 496 / 454 (491), B 16384
-// 634 / 530 / 717 (582), B 32768 939 / 905 / 1259 (1205; 2 lanes, the same
-// rounds, 1229); FP64: B 8192 1264 / 997 / 935 (934), B 16384 1340 / 1126 / 1513
-// (1267); arm (8 / 16 lanes), mixed: B 8192 11918 / 8545 (7804), B 16384 13810 /
-// 13104 (11400), B 32768 21735 / 22296 (23435); FP64: B 8192 17968 / 14932
-// (13468), B 12000 20120 / 21328 (24310).  The linear-quadratic kernels have
-// nothing to share and are slower in wider groups (6 states, FP64, B 16384: 4 /
-// 8 lanes 2176 / 3090).
-int default_group(const Launcher* L, int B, int precision, int device) {
-  if (L->schedule == CBIC_SCHED_GROUP) return (precision == CBIC_FP64 || B <= cu_count(device)) ? 1 : 2;
+// SIMDs once (65536 lanes), for every instance, so that the work counters of a
+// batch do not depend on what follows.  The other work of a group, the
+// derivative blocks and the arm's columns, shares out over more lanes than
+// that, which shortens each instance's chain and costs the chip more waves.  It
+// pays while the chip has room: where the instances end at different times
+// (horizons of their own, a tolerance stop) far more often than where all run
+// the same steps, and less where a wave needs many registers or much LDS time
+// (FP64, the arm's bound).  Measured with six iterations over 50 steps (or a
+// tolerance stop within 20 over 80; ragged horizons from a quarter of those on),
+// time of groups as wide as their rounds / of 8 / of 16 lanes, in ms:
+//   arm, mixed, one horizon: B 8192 .99 / - / .84, 9700 1.32 / 1.33 / 1.31, 16384
+//     1.30 / 1.43 / 1.65, 32768 2.73 / 3.28 / -; ragged: 16384 1.18 / 1.03 / 1.04, 65536
+//     4.39 / 4.24 / -; with a bound: 32768 2.83 / 5.65 / -, ragged 2.64 / 3.75 / -
+//   arm, FP64, one horizon: B 4900 1.29 / - / 1.60, 16384 2.14 / 2.78 / -; with a
+//     tolerance: 6900 6.98 / - / 6.95, 8192 7.83 / - / 8.34; ragged: 8192 1.25 / - / 1.10,
+//     38800 5.28 / 5.18 / -, 46400 5.46 / 6.05 / -
+//   point mass, mixed, one horizon: B 8192 .40 / - / .44, 16384 .66 / .62 / -, 19400
+//     1.26 / 1.32 / -, 32768 1.38 / 1.64 / -; with a tolerance: 32768 2.07 / 1.95 / -, 65536
+//     4.90 / 4.30 / -; ragged: 46400 2.29 / 2.25 / -, 55200 2.47 / 2.64 / -
+// The linear-quadratic kernels have nothing to share and are slower in wider
+// groups (6 states, FP64, B 16384: 4 / 8 lanes 2176 / 3090 us).
+struct WideLimits {
+  long w16, w8;  // the most lanes of a batch in groups of 16, of 8
+  long from8;    // lanes in groups of 8 up to which those do not pay either
+};
+static WideLimits wide_limits(const Launcher* L, const cbic_solve_opts* o, bool ragged) {
+  constexpr long S = 65536, ANY = LONG_MAX;
+  const bool f32 = L->elem == 4, bound = std::isfinite(o->u_max), lm = o->regularization == CBIC_REG_LM,
+             stop = o->stop_mode == 1;
+  if (L->N == 4) {  // point mass
+    if (stop) return {2 * S, ANY, 0};
+    if (ragged) return {2 * S, (f32 ? 6 : 4) * S, 0};
+    return {lm ? 2 * S : S, f32 ? 9 * S / 4 : S, 0};
+  }
+  // arm
+  if (ragged) {
+    if (f32) return {4 * S, bound ? 5 * S / 2 : ANY, 0};
+    return {2 * S, bound || lm ? 5 * S / 2 : 5 * S, 0};
+  }
+  if (f32) {
+    if (lm && !bound) return {4 * S, ANY, 0};
+    if (stop) return {3 * S, bound ? S : 7 * S / 2, 2 * S};
+    return {5 * S / 2, S, 0};
+  }
+  if (bound) return {S, S, 0};
+  if (lm) return {2 * S, S, 0};
+  return stop ? WideLimits{7 * S / 4, 3 * S, 2 * S} : WideLimits{S, S, 0};
+}
+
+int default_group(const Launcher* L, int B, const cbic_solve_opts* o, bool ragged, int device) {
+  if (L->schedule == CBIC_SCHED_GROUP) return (o->precision == CBIC_FP64 || B <= cu_count(device)) ? 1 : 2;
   int trials = 1;
   while (trials < 16 && long(B) * trials * 2 <= 65536) trials *= 2;
   if (L->wide_lanes == 0) return trials;
-  const int lanes = long(B) * 16 <= L->wide_lanes ? 16 : 8;
-  return group_code(lanes > trials ? lanes : trials, trials);
+  const WideLimits w = wide_limits(L, o, ragged);
+  int lanes = trials;
+  if (long(B) * 16 <= std::min(w.w16, L->wide_lanes)) lanes = 16;
+  else if (long(B) * 8 > w.from8 && long(B) * 8 <= w.w8) lanes = 8;
+  return group_code(std::max(lanes, trials), trials);
 }
 
 int requested_group(const Launcher* L, const cbic_solve_opts* o) {

@@ -85,9 +85,9 @@ struct Launcher {
   hipError_t (*iterate_final)(const double* prm, void* base, int Bcap, int Tcap, int nthreads,
                               const int32_t* slots, const SolveParamsH& sp, int G, int group, const IterTrace& tr,
                               int Tmax, int lookahead, const FinalOutH& o, hipStream_t st) = nullptr;
-  // lanes of a batch up to which its groups widen to 16 lanes (0: the groups
-  // are as wide as the line-search rounds)
-  int wide_lanes = 0;
+  // lanes of a batch for which there are kernels of 16-lane groups with fewer
+  // trials (0: the groups are as wide as the line-search rounds)
+  long wide_lanes = 0;
 };
 
 const Launcher* find_launcher(int kind, int n, int m, int precision, int schedule);
@@ -103,10 +103,10 @@ SolveParamsH solve_params(const cbic_solve_opts* o);
 constexpr int group_code(int lanes, int trials) { return lanes | (trials == lanes ? 0 : trials << 8); }
 // the schedule choice when the caller leaves it to the library: lanes per
 // instance and trials per line-search round of the lane schedule (see
-// runtime.cpp), instances per compute unit of the workgroup schedule (one
-// while the batch fits the device's compute units one instance each, two
-// above; always one in FP64)
-int default_group(const Launcher* L, int B, int precision, int device);
+// runtime.cpp; ragged: the instances have horizons of their own), instances
+// per compute unit of the workgroup schedule (one while the batch fits the
+// device's compute units one instance each, two above; always one in FP64)
+int default_group(const Launcher* L, int B, const cbic_solve_opts* o, bool ragged, int device);
 // the caller's own choice for the launcher's schedule (0: none)
 int requested_group(const Launcher* L, const cbic_solve_opts* o);
 // compute units of a device (cached)

@@ -40,3 +40,20 @@ def test_lq_trial_budget_of_any_size(ctx, n, m, trials, prec):
     assert np.all(ref["work"][:, 0] >= 2)
     for g in (2, 4, 8, 16):
         _equal(ref, gpu_solve(ctx, I.SYS_LQ, p, x0, 40, group_lanes=g, **o), [k for k in FIELDS if k != "work"], f"{g}")
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
+@pytest.mark.parametrize("kind", [I.SYS_POINT_MASS, I.SYS_PLANAR3], ids=["pm", "arm"])
+@pytest.mark.parametrize("form", [{}, {"u_max": 4.0}, {"regularization": 1}, {"iters_per_launch": 2},
+                                  {"ls_max_trials": 5}, {"stop_mode": 1, "rtol": 1e-4}],
+                         ids=["clip", "bound", "lm", "launches", "odd_trials", "stop"])
+@pytest.mark.parametrize("ragged", [False, True], ids=["one", "ragged"])
+@pytest.mark.parametrize("B,trials", [(4097, 8), (8193, 4), (16385, 2)])
+def test_own_choice_matches_narrow_groups(ctx, kind, prec, form, ragged, B, trials):
+    # whatever lanes the library takes for a large batch, of one horizon or of
+    # several, every output and the work counters equal those of groups as wide
+    # as the batch's line-search rounds
+    p = I.point_mass_params(0) if kind == I.SYS_POINT_MASS else I.planar3_params(0)
+    x0 = I.point_mass_x0(B, 5) if kind == I.SYS_POINT_MASS else I.planar3_x0(B, 5)
+    o = dict(T=I.horizons(B, 1, 19, 6) if ragged else None, precision=prec, max_iter=3, trace=True, **form)
+    _equal(gpu_solve(ctx, kind, p, x0, 19, group_lanes=trials, **o), gpu_solve(ctx, kind, p, x0, 19, **o))
