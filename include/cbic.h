@@ -282,12 +282,14 @@ cbic_status cbic_solve_batch_noalloc(cbic_context* ctx, const cbic_system* sys, 
  * and remember the fastest in the context for solves of the same system kind,
  * precision, stop rule, iteration budget, batch size (rounded up to a power of
  * two) and T_max.  The candidates are the lanes-per-instance widths 1, 2, 4,
- * 8, 16 on the lane schedule (used by solves whose group_lanes is 0), and one
- * or two instances per compute unit on the workgroup schedule in the mixed
- * precision (used by solves whose wg_per_cu is 0; an FP64 workgroup solve has
- * the one choice 1).  Blocks until done; allocates scratch outputs.  No
- * candidate changes results (the line-search rule picks the same step).
- * *best_group / *best_ms (may be NULL) receive the choice (the width, or the
+ * 8, 16 on the lane schedule and the choice that the library makes for the
+ * batch untuned, which may have fewer line-search trials per round than lanes
+ * (used by solves whose group_lanes is 0), and one or two instances per compute
+ * unit on the workgroup schedule in the mixed precision (used by solves whose
+ * wg_per_cu is 0; an FP64 workgroup solve has the one choice 1).  Blocks until
+ * done; allocates scratch outputs.  No candidate changes results (the
+ * line-search rule picks the same step).
+ * *best_group / *best_ms (may be NULL) receive the choice (its lanes, or the
  * instances per compute unit) and its time. */
 cbic_status cbic_autotune(cbic_context* ctx, const cbic_system* sys, int32_t B, int32_t T_max, const int32_t* d_T,
                           const double* d_x0, const double* d_U0, const cbic_solve_opts* opts, void* stream,

@@ -312,10 +312,10 @@ def solve_batch_noalloc(ctx: Context, sys: System, x0, T_max: int, out: Outputs,
 
 def autotune(ctx: Context, sys: System, x0, T_max: int, T=None, U0=None, opts: Options | None = None,
              stream=None):
-    """Time every schedule candidate on this problem (lanes per instance, or
-    the workgroup schedule's instances per compute unit); the context keeps
-    the fastest for later solves that leave the choice at 0.  Returns
-    (choice, ms)."""
+    """Time every schedule candidate on this problem (lanes per instance, the
+    library's own choice among them, or the workgroup schedule's instances per
+    compute unit); the context keeps the fastest for later solves that leave
+    the choice at 0.  Returns (choice, ms)."""
     import torch
     opts = opts or Options()
     dev = torch.device("cuda", ctx.device)

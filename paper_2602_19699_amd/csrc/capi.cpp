@@ -200,11 +200,12 @@ cbic_status param_block(cbic_system* s, double eps, hipStream_t stream, bool may
 // Enqueue one solve on `stream` with its workspace at `base`: ws_main bytes
 // of the launcher's layout followed by the horizon sort's scratch.  The caller
 // holds ctx->mu with the context's device current.  Allocates nothing itself
-// (a graph launch builds its cached graph on first use).
+// (a graph launch builds its cached graph on first use).  `group`: the schedule
+// choice (0: the caller's, the tuned or the library's own).
 cbic_status enqueue_solve(cbic_context* ctx, const cbic_system* sys, const double* prm, const Launcher* L,
                           const SolveParamsH& sp, int B, int Tmax, const int32_t* d_T, const double* d_x0,
                           const double* d_U0, const cbic_solve_opts* opts, const cbic_outputs* out, char* base,
-                          size_t ws_main, hipStream_t stream) {
+                          size_t ws_main, hipStream_t stream, int group) {
   // the launches below report through hipGetLastError: drop an error another
   // call on this thread left behind
   (void)hipGetLastError();
@@ -236,7 +237,7 @@ cbic_status enqueue_solve(cbic_context* ctx, const cbic_system* sys, const doubl
                               stream));
   }
   if (timing) HIP_TRY(hipEventRecord(ctx->phase_ev[1], stream));
-  int group = requested_group(L, opts);
+  if (group <= 0) group = requested_group(L, opts);
   if (group <= 0) {
     auto it = ctx->tuned.find(tune_key(sys, B, Tmax, opts));
     group = it != ctx->tuned.end() ? it->second : default_group(L, B, opts, d_T != nullptr, ctx->device);
@@ -326,6 +327,33 @@ cbic_status scratch_address(int device, void** out) {
 }
 
 }  // namespace
+
+cbic_status solve_batch_as(cbic_context* ctx, const cbic_system* sys, int B, int Tmax, const int32_t* d_T,
+                           const double* d_x0, const double* d_U0, const cbic_solve_opts* opts,
+                           const cbic_outputs* out, hipStream_t stream, int group) {
+  const Launcher* L = nullptr;
+  cbic_status st = check_solve(ctx, sys, B, Tmax, d_T, d_x0, d_U0, opts, out, &L);
+  if (st) return st;
+  const SolveParamsH sp = solve_params(opts);
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  HIP_TRY(hipSetDevice(ctx->device));
+  // the LQ Hessians are constant; a solve with another clip floor (or the
+  // Levenberg-Marquardt variant, which clips nothing) uses a block of its own
+  const double* prm = nullptr;
+  st = param_block(const_cast<cbic_system*>(sys), sp.eps, stream, true, &prm);
+  if (st) return st;
+  const size_t ws_main = L->ws_bytes(B, Tmax);
+  st = ensure_ws(ctx, ws_main + sort_bytes(B, Tmax));
+  if (st) return st;
+  if (ctx->have_last && ctx->last_stream != stream) HIP_TRY(hipStreamWaitEvent(stream, ctx->done_ev, 0));
+  st = enqueue_solve(ctx, sys, prm, L, sp, B, Tmax, d_T, d_x0, d_U0, opts, out, static_cast<char*>(ctx->ws),
+                     ws_main, stream, group);
+  if (st) return st;
+  HIP_TRY(hipEventRecord(ctx->done_ev, stream));
+  ctx->last_stream = stream;
+  ctx->have_last = true;
+  return CBIC_OK;
+}
 
 cbic_status context_aux(cbic_context* ctx, size_t need, void** p) {
   if (need > ctx->aux_bytes) {
@@ -500,29 +528,7 @@ cbic_status cbic_workspace_size(const cbic_system* s, int32_t B, int32_t Tmax, c
 cbic_status cbic_solve_batch(cbic_context* ctx, const cbic_system* sys, int32_t B, int32_t Tmax,
                              const int32_t* d_T, const double* d_x0, const double* d_U0,
                              const cbic_solve_opts* opts, const cbic_outputs* out, void* stream_v) {
-  const Launcher* L = nullptr;
-  cbic_status st = check_solve(ctx, sys, B, Tmax, d_T, d_x0, d_U0, opts, out, &L);
-  if (st) return st;
-  const SolveParamsH sp = solve_params(opts);
-  std::lock_guard<std::mutex> lk(ctx->mu);
-  hipStream_t stream = static_cast<hipStream_t>(stream_v);
-  HIP_TRY(hipSetDevice(ctx->device));
-  // the LQ Hessians are constant; a solve with another clip floor (or the
-  // Levenberg-Marquardt variant, which clips nothing) uses a block of its own
-  const double* prm = nullptr;
-  st = param_block(const_cast<cbic_system*>(sys), sp.eps, stream, true, &prm);
-  if (st) return st;
-  const size_t ws_main = L->ws_bytes(B, Tmax);
-  st = ensure_ws(ctx, ws_main + sort_bytes(B, Tmax));
-  if (st) return st;
-  if (ctx->have_last && ctx->last_stream != stream) HIP_TRY(hipStreamWaitEvent(stream, ctx->done_ev, 0));
-  st = enqueue_solve(ctx, sys, prm, L, sp, B, Tmax, d_T, d_x0, d_U0, opts, out, static_cast<char*>(ctx->ws),
-                     ws_main, stream);
-  if (st) return st;
-  HIP_TRY(hipEventRecord(ctx->done_ev, stream));
-  ctx->last_stream = stream;
-  ctx->have_last = true;
-  return CBIC_OK;
+  return solve_batch_as(ctx, sys, B, Tmax, d_T, d_x0, d_U0, opts, out, static_cast<hipStream_t>(stream_v), 0);
 }
 
 cbic_status cbic_solve_batch_noalloc(cbic_context* ctx, const cbic_system* sys, int32_t B, int32_t Tmax,
@@ -553,7 +559,7 @@ cbic_status cbic_solve_batch_noalloc(cbic_context* ctx, const cbic_system* sys, 
   st = param_block(const_cast<cbic_system*>(sys), sp.eps, static_cast<hipStream_t>(stream_v), false, &prm);
   if (st) return st;
   return enqueue_solve(ctx, sys, prm, L, sp, B, Tmax, d_T, d_x0, d_U0, opts, out, static_cast<char*>(ctx->scratch),
-                       ws_main, static_cast<hipStream_t>(stream_v));
+                       ws_main, static_cast<hipStream_t>(stream_v), 0);
 }
 
 cbic_status cbic_phase_times(cbic_context* ctx, double* ms3) {

@@ -109,6 +109,9 @@ constexpr int group_code(int lanes, int trials) { return lanes | (trials == lane
 int default_group(const Launcher* L, int B, const cbic_solve_opts* o, bool ragged, int device);
 // the caller's own choice for the launcher's schedule (0: none)
 int requested_group(const Launcher* L, const cbic_solve_opts* o);
+// the choices that cbic_autotune times (out: room for 8), the library's own
+// among them; returns their number
+int tune_candidates(const Launcher* L, int B, const cbic_solve_opts* o, bool ragged, int device, int* out);
 // compute units of a device (cached)
 int cu_count(int device);
 
@@ -152,7 +155,8 @@ struct cbic_context {
     hipGraphExec_t ge = nullptr;
   };
   std::map<std::string, GraphEntry> graphs;
-  // autotuned lanes per instance, keyed by problem class (see autotune.cpp)
+  // autotuned schedule choices (group_code, or instances per compute unit),
+  // keyed by problem class (see autotune.cpp)
   std::map<std::string, int> tuned;
   // small device scratch of the calls beside the solver (the selection of
   // biased initial states), grown on demand
@@ -166,6 +170,12 @@ struct cbic_context {
 // (allocated or grown here; the caller holds ctx->mu and orders its stream
 // after the context's previous call).
 cbic_status context_aux(cbic_context* ctx, size_t need, void** p);
+
+// cbic_solve_batch with a schedule choice of the lane (group_code) or the
+// workgroup schedule, 0: the caller's, the tuned or the library's own.
+cbic_status solve_batch_as(cbic_context* ctx, const cbic_system* sys, int B, int Tmax, const int32_t* d_T,
+                           const double* d_x0, const double* d_U0, const cbic_solve_opts* opts,
+                           const cbic_outputs* out, hipStream_t stream, int group);
 
 struct cbic_system {
   int kind = -1;

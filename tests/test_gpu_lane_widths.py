@@ -57,3 +57,31 @@ def test_own_choice_matches_narrow_groups(ctx, kind, prec, form, ragged, B, tria
     x0 = I.point_mass_x0(B, 5) if kind == I.SYS_POINT_MASS else I.planar3_x0(B, 5)
     o = dict(T=I.horizons(B, 1, 19, 6) if ragged else None, precision=prec, max_iter=3, trace=True, **form)
     _equal(gpu_solve(ctx, kind, p, x0, 19, group_lanes=trials, **o), gpu_solve(ctx, kind, p, x0, 19, **o))
+
+
+def test_a_tuned_solve_is_no_slower_than_an_untuned_one(ctx):
+    # ragged arm batches beyond 8192 instances: the library's own choice (16
+    # lanes, 4 trials per round) takes 0.85 times the best width or less; a
+    # solve after tuning keeps it and its results
+    import torch
+    from paper_2602_19699_amd import cbic
+    B, T = 12000, 40
+    sysm = cbic.System(ctx, I.SYS_PLANAR3, I.planar3_params(0))
+    x0, Td = torch.as_tensor(I.planar3_x0(B, 5), device="cuda"), torch.as_tensor(I.horizons(B, 8, T, 6), device="cuda")
+    o = cbic.Options(precision=1, max_iter=6)
+
+    def solve():
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        out = cbic.solve_batch(ctx, sysm, x0, T, T=Td, opts=o)
+        e1.record()
+        torch.cuda.synchronize()
+        return out, e0.elapsed_time(e1)
+
+    before = min((solve() for _ in range(5)), key=lambda r: r[1])
+    lanes, ms = cbic.autotune(ctx, sysm, x0, T, T=Td, opts=o)
+    after, _ = solve()
+    assert lanes in (1, 2, 4, 8, 16) and ms <= 1.1 * before[1]
+    for k in ("X", "U", "J", "iters", "status", "Vbar", "Vx"):
+        assert torch.equal(getattr(before[0], k), getattr(after, k)), k
+    sysm.close()

@@ -60,3 +60,23 @@ def test_even_batches_that_fill_the_chip_keep_narrow_groups(system, prec, B):
                                                  (PM, 1, 32768, 8), (PM, 0, 16384, 8)])
 def test_ragged_batches_take_wide_groups(system, prec, B, lanes):
     assert choice(system, B, True, precision=prec) == (lanes, rounds(B))
+
+
+@pytest.mark.parametrize("B", [64, 5000, 8193, 16384, 40000])
+@pytest.mark.parametrize("ragged", [False, True])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_the_autotuner_times_the_own_choice(B, ragged, prec):
+    # each width with as many trials as lanes, and what an untuned solve takes,
+    # so that a tuned solve is no slower than an untuned one
+    lib = C.CDLL(cbic.LIB_PATH)
+    find, cands = lib._ZN4cbic13find_launcherEiiiii, lib._ZN4cbic15tune_candidatesEPKNS_8LauncherEiPK15cbic_solve_optsbiPi
+    find.restype = C.c_void_p
+    oc = cbic.Options(precision=prec).c()
+    for system in (PM, ARM, LQ):
+        out = (C.c_int * 8)()
+        n = cands(C.c_void_p(find(*system, prec, 0)), B, C.byref(oc), ragged, 0, out)
+        got = [(c & 0xFF, (c >> 8) or (c & 0xFF)) for c in out[:n]]
+        assert got[:5] == [(g, g) for g in (1, 2, 4, 8, 16)] and len(set(got)) == n
+        assert choice(system, B, ragged, precision=prec) in got
+    n = cands(C.c_void_p(find(I.SYS_QUAD_SYNTH, 37, 12, prec, 0)), B, C.byref(oc), ragged, 0, out)
+    assert list(out[:n]) == ([1, 2] if prec else [1])
