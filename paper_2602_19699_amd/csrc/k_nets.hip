@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(kNetWG) mlp_score(MlpDev net, MlpLds L, int B,
   const bool valid = b < B;
   const double* xb = x + size_t(valid ? b : 0) * n;
   const float tau = (T && valid) ? float(Tmax - T[b]) * (1.0f / float(Tmax)) : 0.0f;
-  const nf4 y = mlp_tile<W, ACT>(net, L, lds, [&](int s, int g) {
+  const nf4 y = mlp_tile<W, 0, ACT>(net, L, lds, [&](int s, int g) {
     const int f = 4 * s + g;
     return !valid ? 0.0f : (f < n ? float(xb[f]) : (f == n && T ? tau : 0.0f));
   });
@@ -69,7 +69,7 @@ __global__ void __launch_bounds__(kNetWG) mlp_rows(MlpDev net, MlpLds L, int B, 
   const int b = (blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6)) * 16 + (lane & 15);
   const bool valid = b < B;
   const float* ib = in + size_t(valid ? b : 0) * net.in_dim;
-  const nf4 y = mlp_tile<W, ACT>(net, L, lds, [&](int s, int gg) {
+  const nf4 y = mlp_tile<W, 0, ACT>(net, L, lds, [&](int s, int gg) {
     const int f = 4 * s + gg;
     return valid && f < net.in_dim ? ib[f] : 0.0f;
   });
@@ -620,19 +620,121 @@ __global__ void __launch_bounds__(4 * W) actor_rollout(const double* __restrict_
   }
 }
 
+// The same rollout with a whole network per wave: 16 instances per wave, four
+// waves per workgroup, the weights read from LDS every step; bit for bit the
+// results of actor_rollout.  A step of a wave alone takes longer (one wave
+// issues the whole network), but a batch needs a quarter of the waves (half of
+// them with 32 neurons) and no barriers, which wins once the chip is full of
+// waves (wave_per_tile).
 template <class Sys, int W, int ACT>
-hipError_t launch_actor_k(const double* prm, const MlpDev& net, int B, int Tmax, const int32_t* d_T,
+__global__ void __launch_bounds__(kNetWG) actor_rollout_wave(const double* __restrict__ prm, MlpDev net, MlpLds L,
+                                                             int B, int Tmax, const int32_t* __restrict__ Tin,
+                                                             const int32_t* __restrict__ perm,
+                                                             const double* __restrict__ x0, double* __restrict__ U,
+                                                             double* __restrict__ X) {
+  constexpr int N = Sys::N, M = Sys::M;
+  constexpr int IN4 = (N + 1 + 3) & ~3;
+  static_assert(M <= 4, "outputs of lane group 0");
+  extern __shared__ float lds[];
+  mlp_stage(net, L, lds);
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int slot = (blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6)) * 16 + c;
+  const bool valid = slot < B;
+  const int b = valid ? (perm ? perm[slot] : slot) : 0;
+  const typename Sys::template Model<double> mdl{prm};
+  const int Tr = valid ? (Tin ? Tin[b] : Tmax) : 0;
+  const int T = (Tr < 1 || Tr > Tmax) ? 0 : Tr;
+  int Tw = T;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) Tw = max(Tw, __shfl_xor(Tw, o, 64));
+  const bool writer = valid && g == 0;
+  double* Ub = U + size_t(valid ? b : 0) * Tmax * M;
+  double* Xb = X ? X + size_t(valid ? b : 0) * (Tmax + 1) * N : nullptr;
+  double x[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = T > 0 ? x0[size_t(b) * N + i] : 0.0;
+  if (writer && Xb)
+#pragma unroll
+    for (int i = 0; i < N; ++i) Xb[i] = x[i];
+  const float inv_T = 1.0f / float(Tmax);
+  for (int k = 0; k < Tw; ++k) {
+    float f[IN4];
+#pragma unroll
+    for (int i = 0; i < IN4; ++i) f[i] = i < N ? float(x[i < N ? i : 0]) : (i == N ? float(Tmax - T + k) * inv_T : 0.0f);
+    const nf4 y = mlp_tile<W, IN4, ACT>(net, L, lds, [&](int s, int gg) {
+      return gg == 0 ? f[4 * s] : (gg == 1 ? f[4 * s + 1] : (gg == 2 ? f[4 * s + 2] : f[4 * s + 3]));
+    });
+    // outputs 0..M-1 of instance c sit in lane c (group 0), registers 0..M-1
+    double u[M];
+#pragma unroll
+    for (int o = 0; o < M; ++o) u[o] = double(__shfl(y[o], c, 64));
+    if (k < T) {
+      double xn[N];
+      mdl.dyn(x, u, xn);
+#pragma unroll
+      for (int i = 0; i < N; ++i) x[i] = xn[i];
+      if (writer) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) Ub[size_t(k) * M + i] = u[i];
+        if (Xb)
+#pragma unroll
+          for (int i = 0; i < N; ++i) Xb[size_t(k + 1) * N + i] = x[i];
+      }
+    }
+  }
+  if (writer) {
+    for (int k = T; k < Tmax; ++k)
+#pragma unroll
+      for (int i = 0; i < M; ++i) Ub[size_t(k) * M + i] = 0.0;
+    if (Xb)
+      for (int k = T + 1; k <= Tmax; ++k)
+#pragma unroll
+        for (int i = 0; i < N; ++i) Xb[size_t(k) * N + i] = 0.0;
+  }
+}
+
+// Which of the two: with one horizon the wave kernel takes a step's time for
+// every 16384 instances begun (one wave per SIMD), the other one grows with the
+// batch, so it is taken while less than a share of the last 16384 is filled.
+// Ragged batches empty as they go, and the split pays up to larger ones.  The
+// lines lie where the two measured alike at horizons up to 60; the arm's
+// dynamics, which one wave of a block steps while the others wait, bring them
+// down.  us, split / wave: 64-64 network, point mass, one horizon: B 8192 93 /
+// 164, 16384 184 / 165, 20480 211 / 261, 32768 331 / 264; ragged: 16384 113 / 177, 32768 292 /
+// 306, 65536 550 / 515; arm, one horizon: 16384 263 / 209, 65536 918 / 601; one layer of
+// 32, arm: 4096 80 / 86, 8192 115 / 87.
+bool wave_per_tile(bool arm, int W, int depth, int B, bool ragged) {
+  const int d = depth < 4 ? depth - 1 : 3, w = W == 64;
+  if (ragged) {
+    static constexpr int most[2][2][4] = {{{1, 8, 16, 16}, {5, 8, 12, 12}}, {{1, 3, 6, 6}, {5, 6, 10, 12}}};  // of 4096
+    return B > 4096 * most[arm][w][d];
+  }
+  static constexpr int share[2][2][4] = {{{25, 25, 70, 75}, {50, 75, 80, 85}}, {{25, 25, 25, 25}, {50, 70, 75, 80}}};  // %
+  const int rounds = B / 16384 + (B % 16384 != 0);
+  return long(B) * 100 > long(share[arm][w][d]) * 16384 * rounds;
+}
+
+template <class Sys, int W, int ACT>
+hipError_t launch_actor_k(const double* prm, const MlpDev& net, const MlpLds& L, int B, int Tmax, const int32_t* d_T,
                           const int32_t* perm, const double* x0, double* U, double* X, hipStream_t st) {
-  hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), dim3((B + 15) / 16), dim3(4 * W), 0, st, prm, net, B, Tmax, d_T,
-                     perm, x0, U, X);
+  if (wave_per_tile(Sys::kSemiImplicit, W, net.depth, B, d_T != nullptr)) {
+    const size_t lds = size_t(L.total()) * sizeof(float);
+    hipError_t e = allow_lds(actor_rollout_wave<Sys, W, ACT>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((actor_rollout_wave<Sys, W, ACT>), dim3((B + kNetWG / 4 - 1) / (kNetWG / 4)), dim3(kNetWG), lds,
+                       st, prm, net, L, B, Tmax, d_T, perm, x0, U, X);
+  } else {
+    hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), dim3((B + 15) / 16), dim3(4 * W), 0, st, prm, net, B, Tmax, d_T,
+                       perm, x0, U, X);
+  }
   return hipGetLastError();
 }
 
 template <class Sys>
-hipError_t launch_actor(const double* prm, const MlpDev& net, int W, int B, int Tmax, const int32_t* d_T,
+hipError_t launch_actor(const double* prm, const MlpDev& net, const MlpLds& L, int B, int Tmax, const int32_t* d_T,
                         const int32_t* perm, const double* x0, double* U, double* X, hipStream_t st) {
-#define CBIC_ACTOR(WW, AA) launch_actor_k<Sys, WW, AA>(prm, net, B, Tmax, d_T, perm, x0, U, X, st)
-  if (W == 32) return net.act == 0 ? CBIC_ACTOR(32, 0) : (net.act == 1 ? CBIC_ACTOR(32, 1) : CBIC_ACTOR(32, 2));
+#define CBIC_ACTOR(WW, AA) launch_actor_k<Sys, WW, AA>(prm, net, L, B, Tmax, d_T, perm, x0, U, X, st)
+  if (L.W == 32) return net.act == 0 ? CBIC_ACTOR(32, 0) : (net.act == 1 ? CBIC_ACTOR(32, 1) : CBIC_ACTOR(32, 2));
   return net.act == 0 ? CBIC_ACTOR(64, 0) : (net.act == 1 ? CBIC_ACTOR(64, 1) : CBIC_ACTOR(64, 2));
 #undef CBIC_ACTOR
 }
@@ -806,6 +908,7 @@ cbic_status cbic_actor_rollout(cbic_context* ctx, const cbic_system* sys, const 
   (void)hipGetLastError();  // launch errors below are this call's, not a stale one
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*actor);
+  const MlpLds w = mlp_lds(actor->in_dim, actor->width, actor->depth, actor->out_dim);
   const bool known = sys->kind == CBIC_SYS_POINT_MASS || sys->kind == CBIC_SYS_PLANAR3 ||
                      (sys->kind == CBIC_SYS_LQ && ((sys->n == 2 && sys->m == 1) || (sys->n == 4 && sys->m == 2) ||
                                                    (sys->n == 6 && sys->m == 3)));
@@ -827,15 +930,15 @@ cbic_status cbic_actor_rollout(cbic_context* ctx, const cbic_system* sys, const 
   }
   hipError_t e;
   if (sys->kind == CBIC_SYS_POINT_MASS) {
-    e = launch_actor<PointMass>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<PointMass>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_PLANAR3) {
-    e = launch_actor<Arm3>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<Arm3>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_LQ && sys->n == 2 && sys->m == 1) {
-    e = launch_actor<LinQuad<2, 1>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<2, 1>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else if (sys->kind == CBIC_SYS_LQ && sys->n == 4 && sys->m == 2) {
-    e = launch_actor<LinQuad<4, 2>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<4, 2>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   } else {
-    e = launch_actor<LinQuad<6, 3>>(sys->d_prm, d, actor->width, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
+    e = launch_actor<LinQuad<6, 3>>(sys->d_prm, d, w, B, T_max, d_T, perm, d_x0, d_U, d_X, st);
   }
   HIP_TRY(e);
   if (perm) {

@@ -107,9 +107,11 @@ __device__ inline void mlp_stage(const MlpDev& net, const MlpLds& L, float* lds)
 }
 
 // The network for the wave's 16 samples.  feat(s, g) returns input feature
-// 4 s + g of this lane's sample (zero past in_dim).  Returns, in lane l,
-// outputs 4 (l / 16) + r (r = 0..3) of sample l % 16 after the output map.
-template <int W, int ACT, class Feat>
+// 4 s + g of this lane's sample (zero past in_dim); IN4 > 0 fixes in4 at
+// compile time (the loop over s is then unrolled, so feat may pick registers
+// with a constant s).  Returns, in lane l, outputs 4 (l / 16) + r (r = 0..3)
+// of sample l % 16 after the output map.
+template <int W, int IN4, int ACT, class Feat>
 __device__ __forceinline__ nf4 mlp_tile(const MlpDev& net, const MlpLds& L, const float* lds, Feat feat) {
   constexpr int NT = W / 16;
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
@@ -126,7 +128,12 @@ __device__ __forceinline__ nf4 mlp_tile(const MlpDev& net, const MlpLds& L, cons
 #pragma unroll
       for (int t = 0; t < NT; ++t) h[t] = mfma_f32_16x16x4(row[16 * t], bv, h[t]);
     };
-    for (int s = 0; s < L.in4 / 4; ++s) kstep(s);
+    if constexpr (IN4 > 0) {
+#pragma unroll
+      for (int s = 0; s < IN4 / 4; ++s) kstep(s);
+    } else {
+      for (int s = 0; s < L.in4 / 4; ++s) kstep(s);
+    }
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
