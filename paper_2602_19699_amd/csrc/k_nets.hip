@@ -33,6 +33,10 @@ hipError_t allow_lds(K kernel, size_t bytes) {
                              int(bytes));
 }
 
+// blocks of `per` that hold n (without the overflow of rounding n up first: n
+// goes up to 2^31 - 1)
+__host__ __device__ constexpr int blocks_of(int n, int per) { return n / per + (n % per != 0); }
+
 __device__ __forceinline__ void sel_clear(uint32_t* __restrict__ sc, int N);
 
 // score[b] = net(x_b, tau_b), tau_b = (T_max - T_b) / T_max (FP64 inputs
@@ -93,11 +97,11 @@ __global__ void __launch_bounds__(kNetWG, 3) mlp_score_r(MlpDev net, int B, int 
   // the selection's scratch, for the launches after this one
   if (sc && blockIdx.x == 0) sel_clear(sc, N);
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-  const int nwaves = gridDim.x * (kNetWG / 64);
+  const int nwaves = gridDim.x * (kNetWG / 64), tiles = blocks_of(B, 16);
   MlpRegs<W, DEPTH> w;
   w.load(net, lane);
   const float inv_T = 1.0f / float(Tmax);
-  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile * 16 < B; tile += nwaves) {
+  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile < tiles; tile += nwaves) {
     const int b = tile * 16 + c;
     const bool valid = b < B;
     const double* xb = x + size_t(valid ? b : 0) * n;
@@ -117,10 +121,10 @@ template <int W, int ACT, int DEPTH>
 __global__ void __launch_bounds__(kNetWG, 3) mlp_rows_r(MlpDev net, int B, const float* __restrict__ in,
                                                         float* __restrict__ out) {
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-  const int nwaves = gridDim.x * (kNetWG / 64);
+  const int nwaves = gridDim.x * (kNetWG / 64), tiles = blocks_of(B, 16);
   MlpRegs<W, DEPTH> w;
   w.load(net, lane);
-  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile * 16 < B; tile += nwaves) {
+  for (int tile = blockIdx.x * (kNetWG / 64) + (threadIdx.x >> 6); tile < tiles; tile += nwaves) {
     const int b = tile * 16 + c;
     const bool valid = b < B;
     const float* ib = in + size_t(valid ? b : 0) * net.in_dim;
@@ -140,7 +144,7 @@ __global__ void __launch_bounds__(kNetWG, 3) mlp_rows_r(MlpDev net, int B, const
 bool regs_take(const MlpDev& d) { return (d.in_dim + 3) / 4 * 4 == kRegIn4 && d.depth <= 2; }
 // blocks for B samples: three waves per SIMD at most, then several tiles a wave
 int reg_blocks(int B, int device) {
-  const int want = (B + kNetWG / 4 - 1) / (kNetWG / 4), most = 3 * cu_count(device);
+  const int want = blocks_of(B, kNetWG / 4), most = 3 * cu_count(device);
   return want < most ? want : most;
 }
 
@@ -710,7 +714,7 @@ bool wave_per_tile(bool arm, int W, int depth, int B, bool ragged) {
     return B > 4096 * most[arm][w][d];
   }
   static constexpr int share[2][2][4] = {{{25, 25, 70, 75}, {50, 75, 80, 85}}, {{25, 25, 25, 25}, {50, 70, 75, 80}}};  // %
-  const int rounds = B / 16384 + (B % 16384 != 0);
+  const int rounds = blocks_of(B, 16384);
   return long(B) * 100 > long(share[arm][w][d]) * 16384 * rounds;
 }
 
@@ -721,10 +725,10 @@ hipError_t launch_actor_k(const double* prm, const MlpDev& net, const MlpLds& L,
     const size_t lds = size_t(L.total()) * sizeof(float);
     hipError_t e = allow_lds(actor_rollout_wave<Sys, W, ACT>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((actor_rollout_wave<Sys, W, ACT>), dim3((B + kNetWG / 4 - 1) / (kNetWG / 4)), dim3(kNetWG), lds,
+    hipLaunchKernelGGL((actor_rollout_wave<Sys, W, ACT>), dim3(blocks_of(B, kNetWG / 4)), dim3(kNetWG), lds,
                        st, prm, net, L, B, Tmax, d_T, perm, x0, U, X);
   } else {
-    hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), dim3((B + 15) / 16), dim3(4 * W), 0, st, prm, net, B, Tmax, d_T,
+    hipLaunchKernelGGL((actor_rollout<Sys, W, ACT>), dim3(blocks_of(B, 16)), dim3(4 * W), 0, st, prm, net, B, Tmax, d_T,
                        perm, x0, U, X);
   }
   return hipGetLastError();
@@ -793,7 +797,7 @@ cbic_status cbic_mlp_forward(cbic_context* ctx, const cbic_mlp* net, int32_t B, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*net);
   const MlpLds L = mlp_lds(net->in_dim, net->width, net->depth, net->out_dim);
-  const dim3 grid((B + kNetWG / 4 - 1) / (kNetWG / 4)), rgrid(reg_blocks(B, ctx->device)), block(kNetWG);
+  const dim3 grid(blocks_of(B, kNetWG / 4)), rgrid(reg_blocks(B, ctx->device)), block(kNetWG);
   const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
 #define CBIC_ROWS(WW, AA)                                                                                    \
@@ -838,11 +842,11 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   const MlpDev d = dev_mlp(*net);
   const MlpLds L = mlp_lds(net->in_dim, net->width, net->depth, net->out_dim);
-  const dim3 grid((Bc + kNetWG / 4 - 1) / (kNetWG / 4)), rgrid(reg_blocks(Bc, ctx->device)), block(kNetWG);
+  const dim3 grid(blocks_of(Bc, kNetWG / 4)), rgrid(reg_blocks(Bc, ctx->device)), block(kNetWG);
   const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
   // scratch of the selection beyond one workgroup's
-  const int G = (Bc + kSelChunk - 1) / kSelChunk;
+  const int G = blocks_of(Bc, kSelChunk);
   uint32_t* sc = nullptr;
   std::unique_lock<std::mutex> lk(ctx->mu, std::defer_lock);
   if (N > 0 && Bc > kSelSmall) {
