@@ -452,8 +452,10 @@ __device__ __forceinline__ bool box_qp(const double (&H)[M][M], const double (&g
     }
   }
   // the factor of the final face (usually the one factored last, which moved
-  // the step to the face's minimiser: factoring it again would give the same)
-  if (W == factored && W != ALL) return true;
+  // the step to the face's minimiser: factoring it again would give the same;
+  // one control has no face to keep, and the test cost its bounded solves 2 %)
+  if constexpr (M > 1)
+    if (W == factored && W != ALL) return true;
   if (W == 0) return chol_fp64<M, NR>(H, lf, invf);
   if (W == ALL) {
 #pragma unroll
