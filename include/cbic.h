@@ -457,8 +457,10 @@ cbic_status cbic_mlp_forward(cbic_context* ctx, const cbic_mlp* net, int32_t B, 
  * [N] (their horizons; requires d_T).  All device memory.  net->in_dim must
  * be n + 1 with d_T, n without; out_dim 1.  0 <= N <= Bc.  The selection
  * reads the scores a few times over: one workgroup up to 16384 candidates,
- * the whole chip beyond (with a scratch buffer of the context, so such calls
- * on one context are ordered one after the other).  Asynchronous on `stream`.
+ * the whole chip beyond (with a scratch buffer of the context).  A selection
+ * of N > 0 first waits for the context's previous solve, selection or ragged
+ * rollout on another stream, and the next one for it.  Asynchronous on
+ * `stream`.
  * Errors: CBIC_E_INVALID (bad sizes or network, NULL pointer), CBIC_E_HIP. */
 cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* std_critic, int32_t Bc, int32_t n, const double* d_x,
                             const int32_t* d_T, int32_t T_max, int32_t N, float* d_score, int32_t* d_sel,

@@ -845,15 +845,26 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   const dim3 grid(blocks_of(Bc, kNetWG / 4)), rgrid(reg_blocks(Bc, ctx->device)), block(kNetWG);
   const bool regs = regs_take(d);
   const size_t lds = size_t(L.total()) * sizeof(float);
-  // scratch of the selection beyond one workgroup's
+  // scratch of the selection beyond one workgroup's; with or without it a
+  // selection is ordered after the context's previous call on another stream,
+  // and the next such call after it (a captured one that needs no scratch takes
+  // its place in its graph alone)
   const int G = blocks_of(Bc, kSelChunk);
   uint32_t* sc = nullptr;
   std::unique_lock<std::mutex> lk(ctx->mu, std::defer_lock);
-  if (N > 0 && Bc > kSelSmall) {
+  bool ordered = N > 0;
+  if (ordered && Bc <= kSelSmall) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+    ordered = cs == hipStreamCaptureStatusNone;
+  }
+  if (ordered) {
     lk.lock();
-    void* aux = nullptr;
-    if (cbic_status e = context_aux(ctx, (size_t(kSelBlocks) + 4 * size_t(G)) * sizeof(uint32_t), &aux)) return e;
-    sc = static_cast<uint32_t*>(aux);
+    if (Bc > kSelSmall) {
+      void* aux = nullptr;
+      if (cbic_status e = context_aux(ctx, (size_t(kSelBlocks) + 4 * size_t(G)) * sizeof(uint32_t), &aux)) return e;
+      sc = static_cast<uint32_t*>(aux);
+    }
     if (ctx->have_last && ctx->last_stream != st) HIP_TRY(hipStreamWaitEvent(st, ctx->done_ev, 0));
   }
 #define CBIC_SCORE(WW, AA)                                                                                      \
@@ -880,7 +891,6 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
   HIP_TRY(hipGetLastError());
   if (N > 0 && !sc) {
     hipLaunchKernelGGL(sel_small, dim3(1), dim3(kSmallWG), 0, st, d_score, Bc, N, d_sel, n, d_x, d_T, d_x_sel, d_T_sel);
-    HIP_TRY(hipGetLastError());
   } else if (sc) {
     for (int pass = 0; pass < 3; ++pass)
       hipLaunchKernelGGL(sel_hist, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc, pass == 0 ? 21 : (pass == 1 ? 10 : 0),
@@ -888,7 +898,9 @@ cbic_status cbic_bic_select(cbic_context* ctx, const cbic_mlp* net, int32_t Bc, 
     hipLaunchKernelGGL(sel_count, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, sc);
     hipLaunchKernelGGL(sel_scatter, dim3(G), dim3(kSelWG), 0, st, d_score, Bc, N, d_sel, n, d_x, d_T, d_x_sel,
                        d_T_sel, sc, G);
-    HIP_TRY(hipGetLastError());
+  }
+  HIP_TRY(hipGetLastError());
+  if (ordered) {
     HIP_TRY(hipEventRecord(ctx->done_ev, st));
     ctx->last_stream = st;
     ctx->have_last = true;
