@@ -168,8 +168,7 @@ typedef struct {
  *   0  the autotuned choice for the problem class (cbic_autotune), else 1 for
  *      batches of at most one instance per compute unit and 2 above
  * FP64 solves always run one instance per compute unit (their shared-memory
- * block is half a compute unit's, and two per unit were slower at every
- * batch size measured).  No result depends on it. */
+ * block, 145 KB, fits a compute unit once).  No result depends on it. */
 
 /* flags */
 #define CBIC_FLAG_GRAPH 1u  /* launch the iteration chain through a captured HIP graph      */

@@ -39,7 +39,10 @@ template <> struct Stride<double> { static constexpr int k = 50; };
 constexpr int SQ = 20;
 constexpr int BROW = 48;                // first LDS row of f_u^T behind f_x^T's three 16-row blocks
 constexpr int DB = (N + M) * KROW;      // derivative block: the 49 columns of [f_x | f_u] as operand rows
-constexpr int CH = 12;                  // steps per chunk of precomputed derivative blocks
+// steps per chunk of precomputed derivative blocks, a multiple of the four
+// waves; 8, 12, 16 and 24 measured within 2 % of each other at every batch size,
+// and the chunk is what a slot's workspace holds beyond its trajectories
+constexpr int CH = 12;
 
 // device block: [dt, w_u, w_T, w_q, w_v, M0 = A^T A (18x18), W1, W2, e(18), x_nom(37)]
 constexpr int O_DT = 0, O_WU = 1, O_WT = 2, O_WQ = 3, O_WV = 4, O_M0 = 5, O_W1 = O_M0 + 324,
@@ -1116,7 +1119,6 @@ __device__ __forceinline__ double wave_trial(Smem<R>& sm, const double* __restri
   // the iterate's step data (x_k; lane (c, part): entries part, part + 4, ...
   // of row c of K_k; u_k and k_k for c) are loaded one step ahead of their use
   constexpr int KQ = (N + 3) / 4;
-  const int c = lane >> 2, part = lane & 3;
   R xq = R(0), uq = R(0), kq = R(0), Kq[KQ];
   auto load = [&](int k) {
     const int lane = fresh(lane_), c = lane >> 2, part = lane & 3;
@@ -1243,10 +1245,12 @@ __global__ void __launch_bounds__(64) quad_init(const double* __restrict__ prm, 
 template <class R, bool BOX, bool LM, int OCC>
 // OCC: workgroups resident per CU the registers are sized for.  With 1 the
 // kernel keeps its values in registers (one wave per SIMD); with 2 the
-// registers are capped at 256 and some values spill, but the per-step chain is
-// latency-bound and a second resident instance per CU hides more of it than
-// the spills cost once the batch fills every CU (mixed, 1024 instances: -35 %;
-// at most one instance per CU: +10 %; FP64 is slower with 2 at every size).
+// registers are capped at 256 and some values spill (28 B of scratch, 304 with
+// the bound), but the per-step chain is latency-bound and a second resident
+// instance per CU hides most of it once the batch fills every CU (mixed, 50
+// steps, four iterations, one / two per CU: 512 instances 6.13 / 4.15 ms, 64
+// instances 3.22 / 3.24).  FP64 is built for one: its 145 KB of LDS fit a CU
+// once.
 // BOX: the variant with the control bound of eq. 1 (sp.umax finite).  LM: the
 // Levenberg-Marquardt variant (sp.reg = 1), in which a failed Cholesky or line search
 // multiplies mu by mu_fac and retries the sweep while mu stays within mu_max;

@@ -194,7 +194,10 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* wtot, uint3
 // blocks done} at kSelState, then per block: greater count, equal count,
 // output base, tie base.  Launch- and latency-bound: 163840 keys take five
 // launches and 41 us, 3000 keys one launch and 13 us; with a launch of its own
-// for every part it was ten launches, 59 and 45 us.
+// for every part it was ten launches, 59 and 45 us.  16384 keys (the most that
+// 1024 threads keep in registers) still take less in one workgroup than 16385
+// over the chip: scoring and selection of a tenth 28 against 48 us, of half 40
+// against 52.
 constexpr int kSelWG = 256, kSelE = 8, kSelChunk = kSelWG * kSelE;
 constexpr int kSelState = 2048, kSelBlocks = 2056;
 constexpr int kSmallWG = 1024, kSmallE = 16, kSelSmall = kSmallWG * kSmallE;
