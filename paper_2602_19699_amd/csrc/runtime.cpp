@@ -77,24 +77,30 @@ int cu_count(int device) {
 
 // Lane schedule: a line-search round tries as many steps as fill the chip's
 // SIMDs once (65536 lanes), for every instance, so that the work counters of a
-// batch do not depend on what follows.  The other work of a group, the
+// batch do not depend on what follows (rounds as wide as the groups would be
+// shorter for some: point mass, mixed, tolerance 1e-4, 16384 instances 530 us
+// with 8 lanes and 8 trials, 560 with the 4 trials taken here; cbic_autotune
+// tries them).  The other work of a group, the
 // derivative blocks and the arm's columns, shares out over more lanes than
 // that, which shortens each instance's chain and costs the chip more waves.  It
 // pays while the chip has room: where the instances end at different times
-// (horizons of their own, a tolerance stop) far more often than where all run
-// the same steps, and less where a wave needs many registers or much LDS time
-// (FP64, the arm's bound).  Measured with six iterations over 50 steps (or a
-// tolerance stop within 20 over 80; ragged horizons from a quarter of those on),
-// time of groups as wide as their rounds / of 8 / of 16 lanes, in ms:
-//   arm, mixed, one horizon: B 8192 .99 / - / .84, 9700 1.32 / 1.33 / 1.31, 16384
-//     1.30 / 1.43 / 1.65, 32768 2.73 / 3.28 / -; ragged: 16384 1.18 / 1.03 / 1.04, 65536
-//     4.39 / 4.24 / -; with a bound: 32768 2.83 / 5.65 / -, ragged 2.64 / 3.75 / -
-//   arm, FP64, one horizon: B 4900 1.29 / - / 1.60, 16384 2.14 / 2.78 / -; with a
-//     tolerance: 6900 6.98 / - / 6.95, 8192 7.83 / - / 8.34; ragged: 8192 1.25 / - / 1.10,
-//     38800 5.28 / 5.18 / -, 46400 5.46 / 6.05 / -
-//   point mass, mixed, one horizon: B 8192 .40 / - / .44, 16384 .66 / .62 / -, 19400
-//     1.26 / 1.32 / -, 32768 1.38 / 1.64 / -; with a tolerance: 32768 2.07 / 1.95 / -, 65536
-//     4.90 / 4.30 / -; ragged: 46400 2.29 / 2.25 / -, 55200 2.47 / 2.64 / -
+// (horizons of their own, a tolerance stop, a fixed budget long enough that
+// converged ones freeze on the way) far more often than where all run the same
+// steps, and less where a wave needs many registers or much LDS time (FP64, the
+// arm's bound).  Time of groups as wide as their rounds / of 8 / of 16 lanes, ms,
+// 50 or 60 steps, ragged horizons from a quarter of those on:
+//   arm, mixed, one horizon, 6 iterations: B 8192 .99 / - / .84, 9700 1.32 / 1.33 / 1.31,
+//     16384 1.30 / 1.43 / 1.65, 32768 2.73 / 3.28 / -; ragged: 16384 1.18 / 1.03 / 1.04,
+//     65536 4.39 / 4.24 / -; with a bound: 32768 2.83 / 5.65 / -, ragged 2.64 / 3.75 / -
+//   arm, FP64, one horizon, 6 iterations: B 4900 1.29 / - / 1.60, 16384 2.14 / 2.78 / -;
+//     ragged: 8192 1.25 / - / 1.10, 38800 5.28 / 5.18 / -, 46400 5.46 / 6.05 / -
+//   point mass, mixed, one horizon, 6 iterations: B 8192 .40 / - / .44, 16384 .66 / .62
+//     / -, 19400 1.26 / 1.32 / -, 32768 1.38 / 1.64 / -; ragged: 46400 2.29 / 2.25 / -, 55200
+//     2.47 / 2.64 / -; with a tolerance: 32768 2.07 / 1.95 / -, 65536 4.90 / 4.30 / -
+// and relative to narrow groups with 50 iterations: arm, mixed, one horizon,
+// 16 lanes: B 4097 .57, 11600 .95, 16384 1.11, 8 lanes: 16385 .72, 23200 1.08, ragged 65536
+// .69; FP64, 16 lanes, one: 4097 .63, 5800 1.26, 8 lanes, ragged: 46400 .93, 65536 1.2;
+// point mass, 8 lanes, one: mixed 65536 .83, FP64 65536 .66.
 // The linear-quadratic kernels have nothing to share and are slower in wider
 // groups (6 states, FP64, B 16384: 4 / 8 lanes 2176 / 3090 us).
 struct WideLimits {
@@ -105,24 +111,25 @@ static WideLimits wide_limits(const Launcher* L, const cbic_solve_opts* o, bool 
   constexpr long S = 65536, ANY = LONG_MAX;
   const bool f32 = L->elem == 4, bound = std::isfinite(o->u_max), lm = o->regularization == CBIC_REG_LM,
              stop = o->stop_mode == 1;
-  if (L->N == 4) {  // point mass
+  // (a budget of up to 12 iterations, 13 to 32, more)
+  const bool more = o->max_iter > 32, mid = !stop && !more && o->max_iter > 12;
+  if (L->N == 4) {  // point mass: converges in 4 iterations (median), 8 (99 %)
     if (stop) return {2 * S, ANY, 0};
+    if (lm && (mid || more)) return {2 * S, f32 ? (ragged ? ANY : 8 * S) : (ragged ? 6 : 3) * S, 0};
+    if (mid || more) return {2 * S, f32 && mid && !ragged ? 5 * S : ANY, 0};
     if (ragged) return {2 * S, (f32 ? 6 : 4) * S, 0};
     return {lm ? 2 * S : S, f32 ? 9 * S / 4 : S, 0};
   }
-  // arm
+  // arm: converges in 56 (median)
   if (ragged) {
-    if (f32) return {4 * S, bound ? 5 * S / 2 : ANY, 0};
-    return {2 * S, bound || lm ? 5 * S / 2 : 5 * S, 0};
+    if (f32 && bound) return {4 * S, more ? 8 * S : 5 * S / 2, 0};
+    if (f32) return {4 * S, mid && !lm ? 7 * S : ANY, 0};
+    if (lm && !bound && (mid || more)) return {2 * S, ANY, 0};
+    return {2 * S, more ? 6 * S : (bound || lm ? 5 * S / 2 : 5 * S), 0};
   }
-  if (f32) {
-    if (lm && !bound) return {4 * S, ANY, 0};
-    if (stop) return {3 * S, bound ? S : 7 * S / 2, 2 * S};
-    return {5 * S / 2, S, 0};
-  }
-  if (bound) return {S, S, 0};
-  if (lm) return {2 * S, S, 0};
-  return stop ? WideLimits{7 * S / 4, 3 * S, 2 * S} : WideLimits{S, S, 0};
+  if (lm && !bound) return f32 ? WideLimits{4 * S, ANY, 0} : WideLimits{2 * S, mid || more ? ANY : S, 0};
+  if (!stop && !more) return {f32 ? 5 * S / 2 : S, S, 0};
+  return {f32 ? 3 * S : 5 * S / 4, bound ? S : 5 * S / 2, 2 * S};
 }
 
 int default_group(const Launcher* L, int B, const cbic_solve_opts* o, bool ragged, int device) {

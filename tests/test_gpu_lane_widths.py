@@ -45,8 +45,8 @@ def test_lq_trial_budget_of_any_size(ctx, n, m, trials, prec):
 @pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "mixed"])
 @pytest.mark.parametrize("kind", [I.SYS_POINT_MASS, I.SYS_PLANAR3], ids=["pm", "arm"])
 @pytest.mark.parametrize("form", [{}, {"u_max": 4.0}, {"regularization": 1}, {"iters_per_launch": 2},
-                                  {"ls_max_trials": 5}, {"stop_mode": 1, "rtol": 1e-4}],
-                         ids=["clip", "bound", "lm", "launches", "odd_trials", "stop"])
+                                  {"ls_max_trials": 5}, {"stop_mode": 1, "rtol": 1e-4}, {"max_iter": 40}],
+                         ids=["clip", "bound", "lm", "launches", "odd_trials", "stop", "budget"])
 @pytest.mark.parametrize("ragged", [False, True], ids=["one", "ragged"])
 @pytest.mark.parametrize("B,trials", [(4097, 8), (8193, 4), (16385, 2)])
 def test_own_choice_matches_narrow_groups(ctx, kind, prec, form, ragged, B, trials):
@@ -55,7 +55,7 @@ def test_own_choice_matches_narrow_groups(ctx, kind, prec, form, ragged, B, tria
     # as the batch's line-search rounds
     p = I.point_mass_params(0) if kind == I.SYS_POINT_MASS else I.planar3_params(0)
     x0 = I.point_mass_x0(B, 5) if kind == I.SYS_POINT_MASS else I.planar3_x0(B, 5)
-    o = dict(T=I.horizons(B, 1, 19, 6) if ragged else None, precision=prec, max_iter=3, trace=True, **form)
+    o = {**dict(T=I.horizons(B, 1, 19, 6) if ragged else None, precision=prec, max_iter=3, trace=True), **form}
     _equal(gpu_solve(ctx, kind, p, x0, 19, group_lanes=trials, **o), gpu_solve(ctx, kind, p, x0, 19, **o))
 
 

@@ -37,8 +37,8 @@ def test_choice_is_a_kernel_and_keeps_the_rounds(B, form):
     for system in (PM, ARM, LQ):
         for prec in (0, 1):
             for ragged in (False, True):
-                for stop in (0, 1):
-                    lanes, trials = choice(system, B, ragged, precision=prec, stop_mode=stop, **form)
+                for stop, it in ((0, 6), (0, 20), (0, 50), (1, 20), (1, 50)):
+                    lanes, trials = choice(system, B, ragged, precision=prec, stop_mode=stop, max_iter=it, **form)
                     assert trials == rounds(B)
                     assert (lanes, trials) in kernels | ({(16, 4)} if system is ARM and prec else set())
                     assert system is not LQ or lanes == trials
@@ -48,11 +48,11 @@ def test_choice_is_a_kernel_and_keeps_the_rounds(B, form):
                                            (ARM, 0, 4097), (ARM, 0, 16384), (ARM, 0, 32768), (ARM, 0, 65536),
                                            (PM, 1, 8192), (PM, 1, 32768), (PM, 1, 65536), (PM, 0, 8192), (PM, 0, 65536)])
 def test_even_batches_that_fill_the_chip_keep_narrow_groups(system, prec, B):
-    # one horizon and a fixed budget: groups wider than their rounds took up to
-    # 1.5 times as long (with the arm's bound 2.1 times)
+    # one horizon and a short fixed budget: groups wider than their rounds took
+    # up to 1.5 times as long (with the arm's bound 2.1 times)
     forms = [{}, dict(u_max=4.0)] if system is ARM else [{}]
     for form in forms:
-        assert choice(system, B, False, precision=prec, **form) == (rounds(B), rounds(B)), form
+        assert choice(system, B, False, precision=prec, max_iter=6, **form) == (rounds(B), rounds(B)), form
 
 
 @pytest.mark.parametrize("system,prec,B,lanes", [(ARM, 1, 8192, 16), (ARM, 1, 16384, 16), (ARM, 1, 65536, 8),
@@ -60,6 +60,13 @@ def test_even_batches_that_fill_the_chip_keep_narrow_groups(system, prec, B):
                                                  (PM, 1, 32768, 8), (PM, 0, 16384, 8)])
 def test_ragged_batches_take_wide_groups(system, prec, B, lanes):
     assert choice(system, B, True, precision=prec) == (lanes, rounds(B))
+
+
+@pytest.mark.parametrize("prec,B", [(1, 16384), (1, 65536), (0, 16384), (0, 65536)])
+def test_long_budgets_of_the_point_mass_take_wide_groups(prec, B):
+    # converged instances freeze on the way: as with a tolerance stop
+    for o in (dict(max_iter=50), dict(max_iter=8, stop_mode=1)):
+        assert choice(PM, B, False, precision=prec, **o) == (8, rounds(B))
 
 
 @pytest.mark.parametrize("B", [64, 5000, 8193, 16384, 40000])
