@@ -26,6 +26,9 @@ lane-schedule solve also finalises the instances; algorithmic bytes or flops
 from the per-instance work counters and the output sizes) and the FP64 CPU
 oracle timed on a bounded sample on this host.
 
+Standard output gets one JSON line of a few kilobytes (`summary`); everything
+measured goes to standard error as a JSON line of its own, some 30 KB.
+
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--quick]
 """
 from __future__ import annotations
@@ -66,20 +69,20 @@ QUAD_SOURCES = ("dev_common.hpp", "ilqr_lane.hpp", "lane_launch.hpp", "runtime.h
 COUNTERS = {
     ("pm16k", "mixed_tol1e-4", "lane_iterate<PointMass,float,8,8,false,true>"): {
         "sources": LANE_SOURCES + ("k_lane_pm.hip",),
-        "sha256": "b3280720cedddfde450289b291187331d2c92ce216d5b82b918e6ff87e2e0f5e",
-        "fetch_kib": 266309.4, "write_kib": 495034.2, "sq_active_inst_valu": 173751351.1,
+        "sha256": "766e4f209c96cf1ba32e33ace4122a2fd28973b3c3f0810f5b16b93e755c2950",
+        "fetch_kib": 265868.4, "write_kib": 494950.6, "sq_active_inst_valu": 173724686.1,
         "profile": "profiles/lane_iterate_pointmass_16k_mixed_tol.md",
     },
     ("arm4k", "mixed_tol1e-7", "lane_iterate<Arm3,float,16,16,false,true>"): {
         "sources": LANE_SOURCES + ("k_lane_arm.hip",),
-        "sha256": "b3e6a63d8d3971d2e03d0c545eb1381d66fb3f411e39ab81251c9566d7b8c912",
-        "fetch_kib": 1476018.0, "write_kib": 12467902.7, "sq_active_inst_valu": 3176856630.5,
+        "sha256": "8de83856cf04b70282b5aef77a5a9e0b78554d2f57eac7588511a468e01f5c73",
+        "fetch_kib": 1476025.0, "write_kib": 12467659.5, "sq_active_inst_valu": 3176774102.5,
         "profile": "profiles/lane_iterate_arm3_4k_mixed_tol.md",
     },
     ("quad1k", "mixed_tol1e-4", "quad_iterate<float,false,false,2>"): {
         "sources": QUAD_SOURCES,
-        "sha256": "0277c277103284108a729ec0e04501f92b54ff7f3c7da2afa934b03219a3d5bb",
-        "fetch_kib": 1105974.9, "write_kib": 2292327.9, "sq_active_inst_valu": 1710327808.0,
+        "sha256": "25f3ed2f4d01938a23eb48ec38606cc2b5cb10cc37d80a42b2ed3cbfcc812f81",
+        "fetch_kib": 1103802.9, "write_kib": 2292323.7, "sq_active_inst_valu": 1708075008.0,
         "profile": "profiles/quad_iterate_1k_mixed_tol.md",
     },
 }
@@ -500,6 +503,31 @@ def fmt(d):
             for k, v in d.items()}
 
 
+def summary(line):
+    """The one line for standard output: the headline with its roofline and CPU
+    baseline, and of everything else the figures that are compared between
+    runs.  Whoever keeps only the end of the output still gets the whole line."""
+    short = {k: line[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                                  "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config", "serial",
+                                  "roofline", "cpu_baseline")}
+
+    def forms(d):
+        return {f: {k: float(f"{v[k]:.4g}") for k in ("ms_per_step", "serial_ms_per_step", "converged_solves_per_s",
+                                                      "max_rel_cost_vs_fp64") if v.get(k) is not None}
+                for f, v in d.items()}
+
+    short["forms"] = forms(line["forms"])
+    short["workloads"] = {w: {"best_form": e["best_form"], "forms": forms(e["forms"])}
+                          for w, e in line["workloads"].items()}
+    if line["serving"]:
+        short["serving"] = {"columns": ["rate", "solves_per_s", "p50_ms", "p99_ms"],
+                            "forms": {f: [[r[k] for k in ("rate", "solves_per_s", "p50_ms", "p99_ms")]
+                                          for r in v["rates"]] for f, v in line["serving"]["forms"].items()}}
+    if line["bic_pipeline"]:
+        short["bic_pipeline"] = {k: v for k, v in line["bic_pipeline"].items() if k.endswith(("_ms", "_per_batch"))}
+    return short
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -625,7 +653,8 @@ def main():
         "serving": serve,
         "bic_pipeline": bic,
     }
-    print(json.dumps(line))
+    print(json.dumps(line), file=sys.stderr, flush=True)
+    print(json.dumps(summary(line)))
 
 
 if __name__ == "__main__":
