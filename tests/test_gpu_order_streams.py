@@ -94,3 +94,31 @@ def test_captured_selection_stands_alone(ctx):
         torch.cuda.synchronize()
         for a, b, c in zip(got, want, again):
             assert torch.equal(a, b) and torch.equal(c, b)
+
+
+def test_many_selections_and_solves_over_three_streams(ctx):
+    # one chain of calls, each on the next stream: a selection from the states of
+    # the solve before it, a solve from the states selected, and so on
+    import torch
+    from paper_2602_19699_amd import cbic
+    N, Tm = 96, 12
+    sysm = cbic.System(ctx, I.SYS_POINT_MASS, I.point_mass_params(0))
+    g = cbic.Mlp(4, 32, 2, 1, torch.as_tensor(I.mlp_params(4, 32, 2, 1, seed=7), device="cuda"))
+    x0 = torch.as_tensor(I.point_mass_x0(N, 8), device="cuda")
+    o = cbic.Options(max_iter=4)
+
+    def chain(streams):
+        xs, outs = x0, []
+        for k in range(12):
+            s = [streams[(2 * k + i) % len(streams)].cuda_stream for i in range(2)]
+            out = cbic.solve_batch(ctx, sysm, xs, Tm, opts=o, stream=s[0])
+            _, _, xs, _ = cbic.bic_select(ctx, g, out.X.view(-1, 4), None, 0, N, gather=True, stream=s[1])
+            outs += [out.J, xs, out]
+        torch.cuda.synchronize()
+        return [v for v in outs if torch.is_tensor(v)]
+
+    one = chain([torch.cuda.Stream()])
+    for _ in range(3):
+        for a, b in zip(one, chain([torch.cuda.Stream() for _ in range(3)])):
+            assert torch.equal(a, b)
+    sysm.close()
